@@ -238,7 +238,11 @@ ocd_status ocd_detect_backward_bce_noalloc(const ocd_problem *pb, const void *H,
  *                         its tile (or its columns, channel_in_registers = 1), so
  *                         that the workgroups dispatched first get their data
  *                         first and start computing while later ones load
- *                         (0: every workgroup loads at once). */
+ *                         (0: every workgroup loads at once).
+ * A detection whose channels several symbols share, or with more than 8 users, carries
+ * the inner products h_u^H r through the Gram matrix instead of the residual (the same
+ * iterates; B >= 2 U, and S >= 3 or U > 8 or B > 256) and runs one workgroup per
+ * subcarrier: of a plan without channel_in_registers it then takes stagger only. */
 typedef struct {
     int lanes_per_vector;
     int vectors_per_block;
@@ -307,8 +311,9 @@ ocd_status ocd_autotune_backward(const ocd_problem *pb, const void *H, const voi
  * z[j] (may be NULL) and llr[j] (may be NULL); every job must use the default
  * regulariser (lambda = NULL), the same storage and the same projection (MMSE,
  * or BOX/HYBRID), and B <= 256.  Jobs are cut into tiles of whole subcarriers,
- * ordered longest-first (LPT), and run by one launch of one kernel: either one
- * workgroup per tile (the hardware dispatcher balances them) or persistent
+ * ordered longest-first (LPT), and run by one kernel, or by one per user bound (8, 16,
+ * 32) for the jobs in the Gram form (see ocd_plan), whose tiles are single subcarriers:
+ * either one workgroup per tile (the hardware dispatcher balances them) or persistent
  * workgroups that pop tiles from a device queue until it is empty.
  *   workspace   device, >= ocd_jobs_workspace_bytes(jobs, n_jobs), 256-byte aligned;
  *               holds the job and tile tables and the queue head.
@@ -327,6 +332,7 @@ ocd_status ocd_autotune_backward(const ocd_problem *pb, const void *H, const voi
  * Lane modes (complex entries per lane, NPL; a job's lanes per vector are B / NPL):
  *   0: NPL = 8 for every job;  1: NPL = 16 for jobs with B > 128, else 8;
  *   2: as 1, and NPL = 4 for jobs with 32 < B <= 128.
+ * (Lane modes and tile policies concern the jobs that carry the residual.)
  * A job whose (lanes, NPL) pair the kernel is not built for keeps NPL = 8; a job
  * with B <= 16 runs at 4 lanes of 8 entries, the antennas past B zero-padded.
  * When the tables change, the call enqueues a host-to-device copy of them from

@@ -170,6 +170,9 @@ bool make_params(const ocd_problem *pb, const ocd_plan &pl, const float *lambda,
     P.lam_default = pb->mode == OCD_BOX ? 0.f : pb->N0 / pb->Es;
     P.sqEs = std::sqrt(pb->Es);
     P.qscale = qam_scale(pb->Q);
+    const int M = 1 << (pb->Q / 2);
+    P.llr_c = 1.5 / (double)(M * M - 1);
+    P.llr_a = 1.0 / std::sqrt((double)pb->Es * P.llr_c);
     P.invU = 1.0f / (float)pb->U;
     set_divisor((unsigned)pb->S, P.divS_m, P.divS_s1, P.divS_s2);
     P.lambda = lambda;
@@ -383,6 +386,9 @@ ocd_status run_forward(const ocd_problem *pb, const ocd_plan &pl, const void *H,
                            z, llr, z_hist, stream);
     }
     const bool f16 = pb->storage == OCD_STORE_F16;
+    // (the history feeds the adjoint, whose training step repeats the residual form's bits)
+    if (!pl.channel_in_registers && !z_hist && gram_form(pb->B, pb->U, pb->S))
+        return launch_gram(f16, P, stream) == hipSuccess ? OCD_OK : OCD_EDEVICE;
     hipError_t e = pl.channel_in_registers
                        ? launch_forward_reg(pl.lanes_per_vector, npl, P.reg_uc, f16, P, threads,
                                             stream)
@@ -547,7 +553,11 @@ static ocd_status autotune_forward(const ocd_problem *pb, int n, const void *con
     }
     repeats = std::max(1, std::min(repeats, 100));
     std::vector<ocd_plan> cands;
+    const bool gram = gram_form(pb->B, pb->U, pb->S);
+    if (gram)   // the Gram form has one mapping: only the staggered starts are left to tune
+        cands.push_back(heuristic_plan(pb, nullptr, false, false));
     for (int L : {4, 8, 16, 32}) {
+        if (gram) break;
         const int cap = 512 / L;
         std::vector<int> vs;
         for (int v = cap; v >= 1 && v >= cap / 16; v /= 2) vs.push_back(v);

@@ -1,0 +1,571 @@
+// ocd_gram.h -- Algorithm 1 for a subcarrier whose channel several symbols share,
+// with the inner products h_u^H r carried instead of the residual r itself.
+//
+// Every update of Algorithm 1 reads r only through q_u = h_u^H r, and r changes only
+// by h_v Delta_v, so the K U updates can be run on the U numbers q (started from the
+// matched filters h_u^H y) and the Gram matrix G = H^H H:
+//   Delta = d_u (q_u - lambda z_u), clipped so that z_u + Delta stays in the box,
+//   z_u += Delta,  q_v -= G_vu Delta  for every v,
+// the iterates of the residual form, update by update.  (d_u (h_u^H r) + p_u z_u with
+// p_u = d_u g_u is z_u + d_u (q_u - lambda z_u).)  H and y are then read once, in one
+// contraction, instead of twice per update: 4 U^2 B / S + 8 U B + 8 K U^2 operations a
+// vector against 16 K U B.
+//
+// One workgroup of four waves per subcarrier (and per 16 symbols of it).
+//   1. The contraction, on the FP32 matrix cores (v_mfma_f32_16x16x4f32).  A row of H or
+//      y is 2B floats; Re h^H x is the dot product of two such rows and Im h^H x that of
+//      x with the row of j h (-Im, Re pairs).  A lane of the matrix operand holds row
+//      l mod 16, and since both operands may permute the summation index alike, its four
+//      K steps take the four floats of one 16-byte load: the operands go from HBM to
+//      registers in the matrix layout, with no staging.  The waves split the antennas.
+//   2. The matrix cores sum only CH x 4 products in FP32; those sums are added in FP64.
+//      A whole sum of 2B products in FP32 leaves an error of 1.5e-7 in z, twice the
+//      residual form's (whose rounding averages over the B entries of r); with FP64
+//      sums of 8 products and FP64 updates it is below it (0.5-0.9 times, B >= 2 U).
+//   3. The four waves' partials meet in LDS; 16 lanes then own one vector and run its
+//      updates in FP64 (full rate on this GPU).  An update is a handful of lane-local
+//      operations, a DPP broadcast of Delta from its owner and two FMAs per lane.
+#pragma once
+
+#include <type_traits>
+#include <utility>
+
+#include "ocd_stage.h"
+
+namespace ocd {
+
+typedef float f32x4_acc __attribute__((ext_vector_type(4)));
+
+constexpr int GRAM_WAVES = 4;
+constexpr int GRAM_THREADS = 64 * GRAM_WAVES;
+constexpr int GRAM_LD = 18;                  // doubles between columns of a 16 x 16 tile in LDS
+constexpr int GRAM_TILE = 16 * GRAM_LD;
+
+// Matrix tiles of a subcarrier with up to UP users.  S8: at most 8 symbols, whose real
+// and imaginary products (or, for UP = 8, whose products beside the Gram columns) share
+// one tile.
+//   UP = 8:  rows are [h; j h], so one product gives Re and Im; tiles G, Q (S8: one)
+//   UP = 16: Re G, Im G, then Re Q, Im Q (S8: one)
+//   UP = 32: Re, Im of G's blocks 00, 01, 11, then Re, Im of Q's blocks 0, 1 (S8: two)
+template <int UP, bool S8>
+struct GramShape {
+    static constexpr int GT = UP == 8 ? (S8 ? 0 : 1) : UP == 16 ? 2 : 6;
+    static constexpr int QT = UP == 8 ? 1 : UP == 16 ? (S8 ? 1 : 2) : (S8 ? 2 : 4);
+    static constexpr int T = GT + QT;
+    static constexpr int HR = UP == 32 ? 2 : 1;          // channel rows per lane
+    static constexpr int GB = 2;                        // 8-antenna blocks loaded together
+    static constexpr int PARTS = UP == 32 ? 2 : 4;       // wave partials kept in LDS
+};
+
+// Sum over the 16 x 16 tile positions this lane holds, in FP64.
+struct GramAcc {
+    double v[4];
+};
+
+// Two complex entries of a row as they are stored, loaded without a branch or a use:
+// entries past B read the row's last valid ones and are zeroed by gram_pair.
+template <bool F16>
+struct GramRaw {
+    typename std::conditional<F16, u32x2_t, f32x4_t>::type v;
+};
+
+template <bool F16, bool VEC>
+__device__ __forceinline__ GramRaw<F16> gram_load(const unsigned char *base, unsigned row, int b, int B)
+{
+    GramRaw<F16> x;
+    if constexpr (VEC) {   // B even, aligned rows: the pair is in or out together
+        const unsigned off = (row * (unsigned)B + min(b, B - 2)) * cbytes<F16>();
+        x.v = *global_ptr(reinterpret_cast<const decltype(x.v) *>(base + off));
+    } else {
+        const unsigned e = row * (unsigned)B;
+        const unsigned o0 = (e + min(b, B - 1)) * cbytes<F16>();
+        const unsigned o1 = (e + min(b + 1, B - 1)) * cbytes<F16>();
+        if constexpr (F16) {
+            x.v.x = *global_ptr(reinterpret_cast<const uint32_t *>(base + o0));
+            x.v.y = *global_ptr(reinterpret_cast<const uint32_t *>(base + o1));
+        } else {
+            const float2 p = global_load2(reinterpret_cast<const float2 *>(base + o0));
+            const float2 q = global_load2(reinterpret_cast<const float2 *>(base + o1));
+            x.v.x = p.x;
+            x.v.y = p.y;
+            x.v.z = q.x;
+            x.v.w = q.y;
+        }
+    }
+    return x;
+}
+
+// The pair as four floats, zero past B (tail: the block is not whole).
+template <bool F16>
+__device__ __forceinline__ float4 gram_pair(const GramRaw<F16> &x, bool tail, int b, int B)
+{
+    float4 q;
+    if constexpr (F16) {
+        const float2 p = half2_to_float2(x.v.x), r = half2_to_float2(x.v.y);
+        q = make_float4(p.x, p.y, r.x, r.y);
+    } else {
+        q = make_float4(x.v.x, x.v.y, x.v.z, x.v.w);
+    }
+    if (tail) {   // the same for the whole wave
+        if (b >= B) q.x = q.y = 0.f;
+        if (b + 1 >= B) q.z = q.w = 0.f;
+    }
+    return q;
+}
+
+// Row of j x beside row x: Re h^H x = <h, x> and Im h^H x = <j h, x> = <h, -j x>.
+__device__ __forceinline__ float4 times_j(float4 q) { return make_float4(-q.y, q.x, -q.w, q.z); }
+__device__ __forceinline__ float4 times_mj(float4 q) { return make_float4(q.y, -q.x, q.w, -q.z); }
+__device__ __forceinline__ float4 pick(bool c, float4 a, float4 b)
+{
+    return make_float4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
+}
+
+// Operands of one 8-antenna block: this lane's channel rows and its symbol row.
+template <int HR, bool F16>
+struct GramBlock {
+    GramRaw<F16> h[HR], y;
+};
+
+template <int UP, bool S8, bool F16, bool VEC>
+__device__ __forceinline__ void gram_load_block(const Params &P, const unsigned char *hb,
+                                                const unsigned char *yb, int blk, int ns,
+                                                GramBlock<GramShape<UP, S8>::HR, F16> &x)
+{
+    const int lane = threadIdx.x & 63, i = lane & 15, b = blk * 8 + (lane >> 4) * 2;
+    const int U = P.U, B = P.B;
+    // rows past the users and symbols repeat a valid one; their products are never read
+    const int hi = UP == 8 ? i & 7 : i;
+    x.h[0] = gram_load<F16, VEC>(hb, min(hi, U - 1), b, B);
+    if constexpr (UP == 32) x.h[1] = gram_load<F16, VEC>(hb, min(16 + i, U - 1), b, B);
+    x.y = gram_load<F16, VEC>(yb, min(S8 ? i & 7 : i, ns - 1), b, B);
+}
+
+__device__ __forceinline__ float comp(const float4 &q, int c)
+{
+    return c == 0 ? q.x : c == 1 ? q.y : c == 2 ? q.z : q.w;
+}
+
+// The products of one block: four K steps into every tile, FP32 sums of 4 CH products.
+template <int UP, bool S8, bool F16, int CH>
+__device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, S8>::HR, F16> &raw,
+                                           int blk, int B, GramAcc (&acc)[GramShape<UP, S8>::T])
+{
+    using Sh = GramShape<UP, S8>;
+    const int b = blk * 8 + ((threadIdx.x >> 4) & 3) * 2;
+    const bool tail = blk * 8 + 8 > B;
+    struct {
+        float4 h[Sh::HR], y;
+    } x;
+#pragma unroll
+    for (int r = 0; r < Sh::HR; ++r) x.h[r] = gram_pair<F16>(raw.h[r], tail, b, B);
+    x.y = gram_pair<F16>(raw.y, tail, b, B);
+    const bool low = (threadIdx.x & 15) < 8;
+    float4 a[2 * Sh::HR];   // rows h and j h
+    float4 bq;              // the symbols' columns
+    if constexpr (UP == 8) {
+        a[0] = a[1] = pick(low, x.h[0], times_j(x.h[0]));
+        bq = S8 ? pick(low, x.h[0], x.y) : x.y;
+    } else {
+#pragma unroll
+        for (int r = 0; r < Sh::HR; ++r) {
+            a[2 * r] = x.h[r];
+            a[2 * r + 1] = times_j(x.h[r]);
+        }
+        bq = S8 ? pick(low, x.y, times_mj(x.y)) : x.y;
+    }
+    const f32x4_acc zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c0 = 0; c0 < 4; c0 += CH) {
+        f32x4_acc d[Sh::T];
+#pragma unroll
+        for (int c = c0; c < c0 + CH; ++c) {
+            auto mm = [&](int t, const float4 &p, const float4 &q) {
+                d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp(p, c), comp(q, c),
+                                                            c == c0 ? zero : d[t], 0, 0, 0);
+            };
+            if constexpr (UP == 8) {
+                if constexpr (!S8) mm(0, a[0], x.h[0]);
+                mm(Sh::T - 1, a[0], bq);
+            } else if constexpr (UP == 16) {
+                mm(0, a[0], x.h[0]);
+                mm(1, a[1], x.h[0]);
+                mm(2, a[0], bq);
+                if constexpr (!S8) mm(3, a[1], bq);
+            } else {
+                mm(0, a[0], x.h[0]);
+                mm(1, a[1], x.h[0]);
+                mm(2, a[0], x.h[1]);
+                mm(3, a[1], x.h[1]);
+                mm(4, a[2], x.h[1]);
+                mm(5, a[3], x.h[1]);
+                mm(6, a[0], bq);
+                if constexpr (S8) {
+                    mm(7, a[2], bq);
+                } else {
+                    mm(7, a[1], bq);
+                    mm(8, a[2], bq);
+                    mm(9, a[3], bq);
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < Sh::T; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t].v[r] += (double)d[t][r];
+    }
+}
+
+// This wave's share of the antennas (whole blocks of 8), the next blocks' loads in
+// flight while the current ones multiply; `between` runs when the first are out.
+template <int UP, bool S8, bool F16, bool VEC, int CH, typename Between>
+__device__ __forceinline__ void gram_contract(const Params &P, const unsigned char *hb,
+                                              const unsigned char *yb, int ns,
+                                              GramAcc (&acc)[GramShape<UP, S8>::T],
+                                              Between &&between)
+{
+    using Sh = GramShape<UP, S8>;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nblk = (P.B + 7) >> 3;
+    const int b0 = wave * nblk / GRAM_WAVES, b1 = (wave + 1) * nblk / GRAM_WAVES;
+    GramBlock<Sh::HR, F16> cur[Sh::GB], nxt[Sh::GB];
+    auto load = [&](GramBlock<Sh::HR, F16> (&x)[Sh::GB], int blk) {   // no branch: clamped
+#pragma unroll
+        for (int i = 0; i < Sh::GB; ++i)
+            gram_load_block<UP, S8, F16, VEC>(P, hb, yb, min(blk + i, nblk - 1), ns, x[i]);
+    };
+    load(cur, b0);
+    load(nxt, b0 + Sh::GB);
+    between();
+    for (int blk = b0; blk < b1; blk += Sh::GB) {
+#pragma unroll
+        for (int i = 0; i < Sh::GB; ++i)
+            if (blk + i < b1) gram_block<UP, S8, F16, CH>(cur[i], blk + i, P.B, acc);
+#pragma unroll
+        for (int i = 0; i < Sh::GB; ++i) cur[i] = nxt[i];
+        if (blk + 2 * Sh::GB < b1) load(nxt, blk + 2 * Sh::GB);
+    }
+}
+
+// LDS position of tile t, column c, row r of a wave partial.
+template <int T>
+__device__ __forceinline__ int gram_at(int part, int t, int c, int r)
+{
+    return (part * T + t) * GRAM_TILE + c * GRAM_LD + r;
+}
+
+// LDS of one subcarrier: the waves' partial tiles, then, in their place, the Gram matrix
+// G[v][u] = h_u^H h_v (column v contiguous) and the matched filters Q[s][u], (re, im).
+template <int UP, bool S8>
+struct GramLds {
+    using Sh = GramShape<UP, S8>;
+    static constexpr int PART = Sh::PARTS * Sh::T * GRAM_TILE;
+    static constexpr int G = 0, Q = 2 * UP * UP;
+    static constexpr int SUMS = Q + (S8 ? 8 : 16) * 2 * UP;
+    static constexpr int DOUBLES = PART > SUMS ? PART : SUMS;
+};
+
+// Per user: ||h_u||^2 and the soft output's constants of llr_coef, L_b = c D_b(a z_u),
+// formed in FP64 (t = a z is of the size of the constellation's levels, and the metrics
+// D_b take differences of it: every rounding of a is one of t).
+struct GramUser {
+    double a;
+    float c, g;
+};
+
+__device__ __forceinline__ GramUser gram_user(const Params &P, float g, float pK, float lamK)
+{
+    const double mu = lamK > 0.f ? (double)pK : 1.0;
+    const double rho = lamK > 0.f ? (double)g / lamK : (double)g * P.Es / P.N0;
+    const bool on = rho > 0.0 && mu > 0.0;   // else a zero column: all of its LLRs are zero
+    return {on ? P.llr_a / mu : 0.0, on ? (float)(rho * P.llr_c) : 0.f, g};
+}
+
+// d_u^-1 of user u of subcarrier w in sweep k, and p_u: the given values, or from
+// g = ||h_u||^2 as k_preprocess forms them.
+__device__ __forceinline__ float gram_dinv(const Params &P, long w, int k, int u, float g,
+                                           float lam, float *p)
+{
+    if (P.dinv_in) {
+        const int Kt = P.per_sweep ? P.K : 1;
+        const long o = (w * Kt + (P.per_sweep ? k : 0)) * P.U + u;
+        *p = global_ptr(P.p_in)[o];
+        return global_ptr(P.dinv_in)[o];
+    }
+    const float den = g + lam;
+    const float di = den > 0.f ? 1.0f / den : 0.f;
+    *p = di * g;
+    return di;
+}
+
+// Contraction of subcarrier w with symbols s0 .. s0 + ns - 1 into lds (GramLds), and the
+// users' constants, ||h_u||^2 in the summation order of k_preprocess, so that d^-1 and p
+// have its bits.  Ends with a workgroup barrier.
+template <int UP, bool S8, bool F16, bool VEC, int CH>
+__device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int ns, double *lds,
+                                           GramUser *us)
+{
+    using Sh = GramShape<UP, S8>;
+    constexpr int T = Sh::T;
+    const int U = P.U, B = P.B;
+    const unsigned char *hb =
+        static_cast<const unsigned char *>(P.H) + (size_t)w * U * B * cbytes<F16>();
+    const unsigned char *yb =
+        static_cast<const unsigned char *>(P.y) + ((size_t)w * P.S + s0) * B * cbytes<F16>();
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+    GramAcc acc[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[t].v[r] = 0.0;
+    // ||h_u||^2: 16 lanes per column, lane l summing entries l, l + 16, ...; the first
+    // 128 antennas of 16 columns are loaded ahead of the operands (the same lines)
+    const int u0 = tid >> 4, l16 = tid & 15;
+    auto entry = [&](int u, int b) -> float2 {
+        const unsigned e = (unsigned)min(u, U - 1) * B + min(b, B - 1);
+        if constexpr (!F16) return global_load2(reinterpret_cast<const float2 *>(hb) + e);
+        else return half2_to_float2(global_ptr(reinterpret_cast<const uint32_t *>(hb))[e]);
+    };
+    auto square = [&](float2 v, int b, float s) {
+        return b < B ? fmaf(v.x, v.x, fmaf(v.y, v.y, s)) : s;
+    };
+    const bool own_g = P.g_in == nullptr, first_g = own_g && (wave * 4 < U);
+    float2 hg[8];
+    if (first_g) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) hg[i] = entry(u0, l16 + 16 * i);
+    }
+    float s0g = 0.f;
+    gram_contract<UP, S8, F16, VEC, CH>(P, hb, yb, ns, acc, [&] {
+        if (first_g) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s0g = square(hg[i], l16 + 16 * i, s0g);
+        }
+    });
+    for (int u = u0; u < U; u += 16) {
+        float s = 0.f;
+        if (own_g) {
+            if (u == u0) s = s0g;
+            for (int b = (u == u0 ? 128 : 0) + l16; b < B; b += 16) s = square(entry(u, b), b, s);
+            s = group_sum<16>(s);
+        } else {
+            s = global_ptr(P.g_in)[w * U + u];
+        }
+        if (l16 == 0) {
+            const float lamK = P.lambda ? global_ptr(P.lambda)[P.K - 1] : P.lam_default;
+            float pK;
+            gram_dinv(P, w, P.K - 1, u, s, lamK, &pK);
+            us[u] = gram_user(P, s, pK, lamK);
+        }
+    }
+
+    const int col = lane & 15, row = (lane >> 4) * 4;
+    auto store = [&](int p) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            double2 *d = reinterpret_cast<double2 *>(lds + gram_at<T>(p, t, col, row));
+            d[0] = make_double2(acc[t].v[0], acc[t].v[1]);
+            d[1] = make_double2(acc[t].v[2], acc[t].v[3]);
+        }
+    };
+    if constexpr (Sh::PARTS == 2) {   // waves 2 and 3 hand theirs to 0 and 1 first
+        if (wave >= 2) store(wave - 2);
+        __syncthreads();
+        if (wave < 2) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const double *d = lds + gram_at<T>(wave, t, col, row);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[t].v[r] += d[r];
+            }
+            store(wave);
+        }
+    } else {
+        store(wave);
+    }
+    __syncthreads();
+    // thread (c, r) sums position (c, r) of every tile over the waves, in wave order
+    const int c = tid >> 4, r = tid & 15;
+    double sum[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        sum[t] = lds[gram_at<T>(0, t, c, r)];
+#pragma unroll
+        for (int p = 1; p < Sh::PARTS; ++p) sum[t] += lds[gram_at<T>(p, t, c, r)];
+    }
+    __syncthreads();
+    double *G = lds + GramLds<UP, S8>::G, *Q = lds + GramLds<UP, S8>::Q;
+    auto put = [&](double *m, int v, int u, int im, double x) { m[2 * (v * UP + u) + im] = x; };
+    if constexpr (UP == 8) {
+        if constexpr (S8) {
+            put(c < 8 ? G : Q, c & 7, r & 7, r >> 3, sum[0]);
+        } else {
+            if (c < 8) put(G, c, r & 7, r >> 3, sum[0]);
+            put(Q, c, r & 7, r >> 3, sum[1]);
+        }
+    } else {
+#pragma unroll
+        for (int im = 0; im < 2; ++im) {
+            put(G, c, r, im, sum[im]);
+            if constexpr (UP == 32) {
+                put(G, 16 + c, r, im, sum[2 + im]);
+                put(G, r, 16 + c, im, im ? -sum[3] : sum[2]);   // block 10 = block 01^H
+                put(G, 16 + c, 16 + r, im, sum[4 + im]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Sh::QT; ++q) {
+            if constexpr (S8) put(Q, c & 7, r + 16 * q, c >> 3, sum[Sh::GT + q]);
+            else put(Q, c, r + 16 * (q >> 1), q & 1, sum[Sh::GT + q]);
+        }
+    }
+    __syncthreads();
+}
+
+// The value of lane N of every aligned group of L = 4 or 16 lanes.
+template <int L, int N>
+__device__ __forceinline__ double group_bcast(double x)
+{
+    constexpr int ctrl = L == 4 ? 0x55 * N : 0x150 + N;   // quad_perm [N,N,N,N]; row_newbcast
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, ctrl, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// f(std::integral_constant<int, 0>) .. f(... N - 1): DPP controls are immediates.
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// Change of one real component: d (q - lambda z), clipped so that z + Delta is in the box.
+template <bool BOX>
+__device__ __forceinline__ double gram_delta(double q, double z, double d, double lam, double beta)
+{
+    const double dl = d * fma(-lam, z, q);
+    if constexpr (!BOX) return dl;
+    return fmin(fmax(z + dl, -beta), beta) - z;
+}
+
+// The K sweeps and the outputs of the workgroup's vectors after gram_front: L lanes per
+// vector, lane i of a group owning users i R .. i R + R - 1 (R = UP / L).  Waves without
+// a vector return at once.
+template <int UP, bool S8, bool BOX, int L>
+__device__ __forceinline__ void gram_sweeps(const Params &P, long w, int s0, int ns,
+                                            const double *lds, const GramUser *us)
+{
+    constexpr int R = UP / L;
+    const int U = P.U, K = P.K;
+    const int i = threadIdx.x % L, s = threadIdx.x / L;
+    if (__builtin_amdgcn_readfirstlane(s) >= ns) return;
+    const bool active = s < ns;
+    const int sv = active ? s : ns - 1;
+    const long v = w * P.S + s0 + sv;
+    const double beta = P.beta;
+    const double2 *G = reinterpret_cast<const double2 *>(lds + GramLds<UP, S8>::G) + i * R;
+    const double2 *Q = reinterpret_cast<const double2 *>(lds + GramLds<UP, S8>::Q) + sv * UP + i * R;
+    double2 q[R], z[R];
+    double d[R], lam = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        q[r] = Q[r];
+        z[r] = make_double2(0.0, 0.0);
+    }
+    auto coefs = [&](int k) {   // users past U: d = 0, never updated
+        const float lf = P.lambda ? global_ptr(P.lambda)[k] : P.lam_default;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int u = i * R + r, uu = min(u, U - 1);
+            float p;
+            const float di = gram_dinv(P, w, k, uu, us[uu].g, lf, &p);
+            d[r] = u < U ? di : 0.f;
+        }
+        lam = lf;
+    };
+    if (!P.per_sweep) coefs(0);
+    for (int k = 0; k < K; ++k) {
+        if (P.per_sweep) coefs(k);
+        static_for<UP / 4>([&](auto cc) {   // four updates at a time (users past U change nothing)
+            constexpr int c = decltype(cc)::value;
+            if (4 * c < U) {
+                static_for<4>([&](auto uc) {
+                    constexpr int u = 4 * c + decltype(uc)::value, o = u / R, n = u % R;
+                    const double cr = gram_delta<BOX>(q[n].x, z[n].x, d[n], lam, beta);
+                    const double ci = gram_delta<BOX>(q[n].y, z[n].y, d[n], lam, beta);
+                    const double dr = group_bcast<L, o>(cr), di = group_bcast<L, o>(ci);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const double2 a = G[u * UP + r];
+                        q[r].x = fma(-a.x, dr, fma(a.y, di, q[r].x));
+                        q[r].y = fma(-a.x, di, fma(-a.y, dr, q[r].y));
+                    }
+                    const double own = i == o ? 1.0 : 0.0;   // the owner's z
+                    z[n].x = fma(own, cr, z[n].x);
+                    z[n].y = fma(own, ci, z[n].y);
+                });
+            }
+        });
+        if (P.z_hist && active) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (i * R + r < U)
+                    global_store2(P.z_hist + (v * K + k) * U + i * R + r,
+                                  make_float2((float)z[r].x, (float)z[r].y));
+        }
+    }
+    if (!active) return;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int u = i * R + r;
+        if (u >= U) continue;
+        if (P.z) global_store2(P.z + v * U + u, make_float2((float)z[r].x, (float)z[r].y));
+        if (P.llr) {
+            const double ua = us[u].a;
+            const float uc = us[u].c;
+            const float tr = (float)(z[r].x * ua), ti = (float)(z[r].y * ua);
+            const int half = P.Q >> 1;
+            const auto dst = global_ptr(P.llr) + (v * U + u) * P.Q;
+            if (half == 3) {
+                axis_llrs<3>(tr, uc, dst);
+                axis_llrs<3>(ti, uc, dst + 3);
+            } else if (half == 2) {
+                axis_llrs<2>(tr, uc, dst);
+                axis_llrs<2>(ti, uc, dst + 2);
+            } else {
+                axis_llrs<1>(tr, uc, dst);
+                axis_llrs<1>(ti, uc, dst + 1);
+            }
+        }
+    }
+}
+
+// How long the FP32 sums of the contraction are (CH of 4 products each; 0: rows without
+// vector loads, sums of 4): 16 products from 128 antennas and four per user on, 8 from 64
+// antennas on, 4 below, the longest whose rounding stays below the residual form's.
+// Error of z at 8-20 dB (residual form; 16, 8, 4 products):
+//   B = 128, U = 8:  5.7e-8; 4.6e-8, 3.7e-8, 3.3e-8     B = 64, U = 16: 8.0e-8; 8.8e-8, 6.6e-8, 5.1e-8
+//   B = 128, U = 32: 8.4e-8; 7.2e-8, 5.2e-8, 4.0e-8     B = 32, U = 16: 1.13e-7; 1.71e-7, 1.19e-7, 9.0e-8
+__host__ __device__ inline int gram_chunk(const Params &P)
+{
+    return !P.vec_ok ? 0 : P.B >= 128 && P.B >= 4 * P.U ? 4 : P.B >= 64 ? 2 : 1;
+}
+
+// One tile: subcarrier w, symbols s0 .. s0 + ns - 1.
+template <int UP, bool S8, bool F16, bool BOX, bool VEC, int CH>
+__device__ __forceinline__ void gram_tile(const Params &P, long w, int s0, int ns, double *lds,
+                                          GramUser *us)
+{
+    gram_front<UP, S8, F16, VEC, CH>(P, w, s0, ns, lds, us);
+    gram_sweeps<UP, S8, BOX, UP == 32 ? 16 : 4>(P, w, s0, ns, lds, us);
+}
+
+}  // namespace ocd

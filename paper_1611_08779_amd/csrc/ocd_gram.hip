@@ -1,0 +1,70 @@
+// ocd_gram.hip -- the detection kernel for channels that several symbols share
+// (ocd_gram.h): one workgroup per subcarrier and per 16 symbols of it.
+#include "ocd_gram.h"
+
+namespace ocd {
+
+// VEC: rows of even length, aligned.  CH: see gram_chunk.
+template <int UP, bool S8, bool F16, bool BOX, bool VEC, int CH>
+__global__ __launch_bounds__(GRAM_THREADS, 2) void k_gram(Params P, int tiles)
+{
+    __shared__ __align__(16) double lds[GramLds<UP, S8>::DOUBLES];
+    __shared__ GramUser us[UP];
+    stagger_loads(P);
+    const int w = tiles == 1 ? (int)blockIdx.x : (int)blockIdx.x / tiles;
+    const int s0 = tiles == 1 ? 0 : 16 * ((int)blockIdx.x - w * tiles);
+    const int ns = min(16, P.S - s0);
+    gram_tile<UP, S8, F16, BOX, VEC, CH>(P, w, s0, ns, lds, us);
+}
+
+template <int UP, bool S8, bool F16, bool BOX, bool VEC, int CH>
+static hipError_t launch_gram_k(const Params &p, hipStream_t s)
+{
+    auto fn = k_gram<UP, S8, F16, BOX, VEC, CH>;
+    Params q = p;
+    const int tiles = (p.S + 15) / 16;
+    if (q.stagger > 0) {
+        int per_cu = 0;
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void *>(fn), GRAM_THREADS, 0);
+        if (e != hipSuccess) return e;
+        q.stagger_cap = per_cu * device_cu_count();
+    }
+    hipLaunchKernelGGL(fn, dim3((unsigned)p.W * tiles), dim3(GRAM_THREADS), 0, s, q, tiles);
+    return hipGetLastError();
+}
+
+template <int UP, bool S8, bool F16, bool BOX>
+static hipError_t launch_gram_c(const Params &p, hipStream_t s)
+{
+    switch (gram_chunk(p)) {
+    case 4: return launch_gram_k<UP, S8, F16, BOX, true, 4>(p, s);
+    case 2: return launch_gram_k<UP, S8, F16, BOX, true, 2>(p, s);
+    case 1: return launch_gram_k<UP, S8, F16, BOX, true, 1>(p, s);
+    default: return launch_gram_k<UP, S8, F16, BOX, false, 1>(p, s);
+    }
+}
+
+template <int UP, bool S8>
+static hipError_t launch_gram_s(bool f16, const Params &p, hipStream_t s)
+{
+    if (f16) return p.box ? launch_gram_c<UP, S8, true, true>(p, s)
+                          : launch_gram_c<UP, S8, true, false>(p, s);
+    return p.box ? launch_gram_c<UP, S8, false, true>(p, s)
+                 : launch_gram_c<UP, S8, false, false>(p, s);
+}
+
+template <int UP>
+static hipError_t launch_gram_u(bool f16, const Params &p, hipStream_t s)
+{
+    return p.S <= 8 ? launch_gram_s<UP, true>(f16, p, s) : launch_gram_s<UP, false>(f16, p, s);
+}
+
+hipError_t launch_gram(bool f16, const Params &p, hipStream_t s)
+{
+    if (p.U <= 8) return launch_gram_u<8>(f16, p, s);
+    if (p.U <= 16) return launch_gram_u<16>(f16, p, s);
+    return launch_gram_u<32>(f16, p, s);
+}
+
+}  // namespace ocd

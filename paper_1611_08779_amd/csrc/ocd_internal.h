@@ -26,6 +26,7 @@ struct Params {
     float lam_default;   // regulariser when lambda == nullptr
     float sqEs;          // sqrt(Es)
     float qscale;        // level spacing of the unit-energy square QAM
+    double llr_a, llr_c; // 1 / (sqEs qscale) and qscale^2 in FP64 (Gram form)
     float invU;          // 1 / U (slot of a staged H row without an integer divide)
     unsigned divS_m;     // n / S = divide_invariant(n, divS_m, divS_s1, divS_s2) (see
     int divS_s1, divS_s2;// set_divisor): exact, with no integer divide on the GPU
@@ -118,6 +119,20 @@ inline bool latency_bound(const Params &p, int threads)
     return cus > 0 && (long)p.nblocks * (threads / 64) <= 2L * 4 * cus;
 }
 
+// Whether a detection carries the inner products h_u^H r through the Gram matrix
+// (ocd_gram.h) instead of the residual.  From B = 2 U on the rounding of the products
+// stays below the residual form's.  The contraction costs the same whatever S and K are,
+// the residual form 2 S K passes over the antennas: measured over B = 32-256, U = 4-32
+// and K = 1-5 the Gram form takes 0.4-0.9 of the residual form's time from S = 4 on and
+// 0.35-1.1 at S = 3.  Below, it still does for U > 8 (0.24-1.06 at S = 1, 2), where the
+// residual form stages a channel that hardly anything shares; up to 8 users the channel
+// fits the registers (ocd_forward_reg.hip) and the residual form takes 0.24-0.9 of the
+// Gram form's time.
+inline bool gram_form(int B, int U, int S)
+{
+    return B >= 2 * U && (U > 8 || S >= 3 || B > 256);
+}
+
 // Launchers (one per template instantiation, selected at run time).
 hipError_t launch_forward(int L, int NPL, bool f16, const Params &p, int threads, size_t lds,
                           hipStream_t s);
@@ -125,6 +140,7 @@ hipError_t launch_backward(int L, int NPL, bool f16, const Params &p, int thread
                            hipStream_t s);
 hipError_t launch_forward_reg(int L, int NPL, int UC, bool f16, const Params &p,
                               int threads, hipStream_t s);
+hipError_t launch_gram(bool f16, const Params &p, hipStream_t s);
 hipError_t launch_mmse(int L, int NPL, bool f16, const Params &p, int threads, size_t lds,
                        hipStream_t s);
 hipError_t launch_mmse_mfma(bool f16, const Params &p, size_t lds, hipStream_t s);

@@ -1,7 +1,8 @@
 // ocd_jobs.hip -- uneven detection jobs in one persistent launch.
 //
 // Every job is cut into tiles of consecutive (subcarrier, symbol) vectors.  A
-// tile runs exactly the one-problem code (forward_tile).  The lanes per vector
+// tile runs exactly the one-problem code: gram_tile for a job in the Gram form (one
+// subcarrier a tile, ocd_jobs_gram.hip, a kernel per user bound), else forward_tile.  The lanes per vector
 // follow from the complex entries each lane holds (NPL): a job with B antennas
 // uses L = B / NPL lanes (4, 8, 16 or 32).  The batch tuner picks one of three
 // lane modes for the whole batch: NPL = 8 for every job; NPL = 16 for jobs with
@@ -29,18 +30,12 @@
 #include <vector>
 
 #include "ocd_api_internal.h"
+#include "ocd_jobs.h"
 #include "ocd_tile.h"
 
 namespace ocd {
 
 constexpr int JOB_THREADS = 512;
-
-struct JobDesc {
-    Params P;
-    int L;
-    int npl;   // complex entries per lane
-    int pad_[2];
-};
 
 // Lane modes of the batch tuner: the complex entries per lane for a job with B
 // antennas (the lanes per vector are then B / NPL, rounded up to a power of two).
@@ -52,13 +47,6 @@ static int lane_mode_npl(int mode, int B)
     if (mode == 2 && B > 32) return 4;
     return 8;
 }
-
-struct TileDesc {
-    int vbase;
-    int job;
-    int nvb;
-    int pad_;
-};
 
 constexpr size_t HEADER_BYTES = 256;
 
@@ -145,21 +133,30 @@ __global__ __launch_bounds__(JOB_THREADS, 4) void k_jobs(const JobDesc *__restri
     }
 }
 
-__global__ void k_reset_queue(unsigned int *next) { *next = 0u; }
+__global__ void k_reset_queue(unsigned int *next)
+{
+    if (threadIdx.x < N_JOB_KERNELS) next[threadIdx.x] = 0u;
+}
 
 // ------------------------------------------------------------------ host planning
 
+// The tiles of a batch: kernel k's are first[k] .. first[k + 1] - 1, longest first.
+struct TileTable {
+    std::vector<TileDesc> tiles;
+    int first[N_JOB_KERNELS + 1] = {};
+};
+
 struct JobsPlan {
     std::vector<JobDesc> jobs;
-    // LPT-ordered tiles; shared and cached per (job shapes, policy), since building
-    // and sorting them costs far more host time than a launch
-    std::shared_ptr<const std::vector<TileDesc>> tiles;
+    // shared and cached per (job shapes, policy), since building and sorting the tiles
+    // costs far more host time than a launch
+    std::shared_ptr<const TileTable> tiles;
     size_t lds_max = 0;
     bool f16 = false, box = false;
 };
 
 static std::mutex g_tiles_mu;
-static std::map<std::string, std::shared_ptr<const std::vector<TileDesc>>> g_tiles;
+static std::map<std::string, std::shared_ptr<const TileTable>> g_tiles;
 static std::string jobs_hash(const ocd_problem *jobs, int n);
 
 // Tile-size policies the batch tuner chooses from:
@@ -181,6 +178,13 @@ static bool job_shape_built(int L, int npl)
 {
     if (npl == 8) return L == 4 || L == 8 || L == 16 || L == 32;
     return (npl == 16 || npl == 4) && (L == 16 || L == 32);
+}
+
+// The kernel that runs a job (see N_JOB_KERNELS).
+static int job_kernel(const Params &P)
+{
+    if (!gram_form(P.B, P.U, P.S)) return 0;
+    return P.U <= 8 ? 1 : P.U <= 16 ? 2 : 3;
 }
 
 static ocd_status plan_jobs(const ocd_problem *jobs, int n, int policy, int lane_mode,
@@ -231,7 +235,7 @@ static ocd_status plan_jobs(const ocd_problem *jobs, int n, int policy, int lane
         jd.L = L;
         jd.npl = npl_t;
         out.jobs.push_back(jd);
-        out.lds_max = std::max(out.lds_max, lds);
+        if (job_kernel(P) == 0) out.lds_max = std::max(out.lds_max, lds);
     }
     char pk[32];
     std::snprintf(pk, sizeof pk, "|p%d|m%d", policy, lane_mode);
@@ -242,28 +246,43 @@ static ocd_status plan_jobs(const ocd_problem *jobs, int n, int policy, int lane
         out.tiles = it->second;
         return OCD_OK;
     }
-    auto tiles = std::make_shared<std::vector<TileDesc>>();
-    for (int j = 0; j < n; ++j) {
-        const Params &P = out.jobs[j].P;
-        const long nvec = (long)P.W * P.S;
-        for (long v = 0; v < nvec; v += P.vpb) {
-            TileDesc td;
-            td.vbase = (int)v;
-            td.job = j;
-            td.nvb = (int)std::min<long>(P.vpb, nvec - v);
-            td.pad_ = 0;
-            tiles->push_back(td);
+    auto table = std::make_shared<TileTable>();
+    // longest processing time first: cost ~ vectors x sweeps x users x padded antennas,
+    // in the Gram form ~ users^2 x antennas + vectors x users x (antennas + sweeps x users)
+    struct Costed {
+        TileDesc t;
+        double cost;
+    };
+    std::vector<Costed> list;
+    for (int k = 0; k < N_JOB_KERNELS; ++k) {
+        list.clear();
+        for (int j = 0; j < n; ++j) {
+            const Params &P = out.jobs[j].P;
+            if (job_kernel(P) != k) continue;
+            const long nvec = (long)P.W * P.S;
+            auto add = [&](long v, long nvb, double cost) {
+                list.push_back({{(int)v, j, (int)nvb, 0}, cost});
+            };
+            if (k == 0) {
+                for (long v = 0; v < nvec; v += P.vpb) {
+                    const long nvb = std::min<long>(P.vpb, nvec - v);
+                    add(v, nvb, (double)nvb * P.K * P.U * P.Bpad);
+                }
+            } else {
+                for (long w = 0; w < P.W; ++w)
+                    for (int s = 0; s < P.S; s += 16) {
+                        const int ns = std::min(16, P.S - s);
+                        add(w * P.S + s, ns,
+                            0.5 * P.U * P.U * P.B + (double)ns * P.U * (P.B + (double)P.K * P.U));
+                    }
+            }
         }
+        std::stable_sort(list.begin(), list.end(),
+                         [](const Costed &a, const Costed &b) { return a.cost > b.cost; });
+        for (const Costed &c : list) table->tiles.push_back(c.t);
+        table->first[k + 1] = (int)table->tiles.size();
     }
-    // longest processing time first: cost ~ vectors x sweeps x users x padded antennas
-    std::vector<double> jcost(n);
-    for (int j = 0; j < n; ++j) {
-        const Params &P = out.jobs[j].P;
-        jcost[j] = (double)P.K * P.U * P.Bpad;
-    }
-    std::stable_sort(tiles->begin(), tiles->end(), [&](const TileDesc &a, const TileDesc &b) {
-        return a.nvb * jcost[a.job] > b.nvb * jcost[b.job];
-    });
+    const std::shared_ptr<const TileTable> tiles = table;
     out.tiles = tiles;
     g_tiles[key] = tiles;
     return OCD_OK;
@@ -271,7 +290,7 @@ static ocd_status plan_jobs(const ocd_problem *jobs, int n, int policy, int lane
 
 static size_t table_bytes(const JobsPlan &jp)
 {
-    return jp.jobs.size() * sizeof(JobDesc) + jp.tiles->size() * sizeof(TileDesc);
+    return jp.jobs.size() * sizeof(JobDesc) + jp.tiles->tiles.size() * sizeof(TileDesc);
 }
 
 // ------------------------------------------------------------------ launch state
@@ -281,7 +300,7 @@ struct Staging {
     size_t bytes = 0;
     hipEvent_t uploaded = nullptr;
     std::vector<unsigned char> last_jobs;           // job table last uploaded here
-    std::shared_ptr<const std::vector<TileDesc>> last_tiles;   // tile table last uploaded here
+    std::shared_ptr<const TileTable> last_tiles;   // tile table last uploaded here
 };
 
 struct GraphEntry {
@@ -321,7 +340,7 @@ static int persistent_grid(const JobsPlan &jp)
     const int by_waves = (4 * 4 * 64) / JOB_THREADS;   // 4 waves per SIMD, 4 SIMDs per CU
     const int by_lds = (int)(lds_cu / std::max<size_t>(jp.lds_max, 1));
     const int per_cu = std::max(1, std::min(by_waves, by_lds));
-    return (int)std::max<long>(1, std::min<long>((long)ncu * per_cu, (long)jp.tiles->size()));
+    return (int)std::max<long>(1, std::min<long>((long)ncu * per_cu, (long)jp.tiles->first[1]));
 }
 
 static hipError_t enqueue_jobs(const JobsPlan &jp, unsigned char *ws, int persistent, hipStream_t s)
@@ -330,9 +349,18 @@ static hipError_t enqueue_jobs(const JobsPlan &jp, unsigned char *ws, int persis
     const JobDesc *jobs = reinterpret_cast<const JobDesc *>(ws + HEADER_BYTES);
     const TileDesc *tiles = reinterpret_cast<const TileDesc *>(ws + HEADER_BYTES +
                                                                jp.jobs.size() * sizeof(JobDesc));
-    const int ntiles = (int)jp.tiles->size();
+    const int *first = jp.tiles->first;
+    if (persistent) hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, s, next);
+    // the kernels with the longest tiles first
+    for (int k = N_JOB_KERNELS - 1; k >= 1; --k) {
+        if (first[k] == first[k + 1]) continue;
+        const hipError_t e = launch_jobs_gram(k, jp.f16, jp.box, jobs, tiles + first[k], next + k,
+                                              first[k + 1] - first[k], persistent, s);
+        if (e != hipSuccess) return e;
+    }
+    const int ntiles = first[1];
+    if (ntiles == 0) return hipSuccess;
     const int grid = persistent ? persistent_grid(jp) : ntiles;
-    if (persistent) hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, s, next);
     if (jp.f16) {
         if (jp.box) hipLaunchKernelGGL((k_jobs<true, true>), dim3(grid), dim3(JOB_THREADS), jp.lds_max, s, jobs, tiles, next, ntiles, persistent);
         else hipLaunchKernelGGL((k_jobs<true, false>), dim3(grid), dim3(JOB_THREADS), jp.lds_max, s, jobs, tiles, next, ntiles, persistent);
@@ -355,7 +383,7 @@ static const void *jobs_kernel(bool f16, bool box)
 // unless the workspace already holds exactly these bytes.
 static hipError_t upload_tables(const JobsPlan &jp, unsigned char *ws, hipStream_t s)
 {
-    const size_t nj = jp.jobs.size() * sizeof(JobDesc), nt = jp.tiles->size() * sizeof(TileDesc);
+    const size_t nj = jp.jobs.size() * sizeof(JobDesc), nt = jp.tiles->tiles.size() * sizeof(TileDesc);
     const size_t bytes = nj + nt;
     Staging &st = g_staging[ws];
     if (st.last_tiles == jp.tiles && st.last_jobs.size() == nj &&
@@ -379,7 +407,7 @@ static hipError_t upload_tables(const JobsPlan &jp, unsigned char *ws, hipStream
     }
     unsigned char *h = static_cast<unsigned char *>(st.pinned);
     std::memcpy(h, jp.jobs.data(), nj);
-    std::memcpy(h + nj, jp.tiles->data(), nt);
+    std::memcpy(h + nj, jp.tiles->tiles.data(), nt);
     e = hipMemcpyAsync(ws + HEADER_BYTES, h, bytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     st.last_jobs.assign(h, h + nj);
@@ -427,7 +455,7 @@ static ocd_status run_choice(const ocd_problem *jobs, int n, int choice, const v
     ocd_status st = plan_jobs(jobs, n, choice_policy(choice), choice_lane_mode(choice), jp);
     if (st != OCD_OK) return st;
     if (HEADER_BYTES + table_bytes(jp) > ws_bytes) return OCD_EINVAL;
-    if (jp.tiles->empty()) return OCD_OK;
+    if (jp.tiles->tiles.empty()) return OCD_OK;
     fill_pointers(jp, H, y, z, llr);
     const void *fn = jobs_kernel(jp.f16, jp.box);
     if (jp.lds_max > 65536 &&
@@ -438,8 +466,10 @@ static ocd_status run_choice(const ocd_problem *jobs, int n, int choice, const v
     if (!use_graph) return enqueue_jobs(jp, ws, persistent, s) == hipSuccess ? OCD_OK : OCD_EDEVICE;
 
     char key[256];
-    std::snprintf(key, sizeof key, "%p|%zu|%zu|%zu|%d|%d|%d", (void *)ws, jp.jobs.size(),
-                  jp.tiles->size(), jp.lds_max, choice, (int)jp.f16, (int)jp.box);
+    const int *first = jp.tiles->first;
+    std::snprintf(key, sizeof key, "%p|%zu|%d|%d|%d|%d|%zu|%d|%d|%d", (void *)ws, jp.jobs.size(),
+                  first[1], first[2], first[3], first[4], jp.lds_max, choice, (int)jp.f16,
+                  (int)jp.box);
     auto it = g_graphs.find(key);
     if (it == g_graphs.end()) {
         if (!g_capture_stream &&
@@ -514,8 +544,15 @@ extern "C" ocd_status ocd_detect_jobs(const ocd_problem *jobs, const void *const
             (void)hipEventElapsedTime(&ms, e0, e1);
             return ms;
         };
+        // tile policies and lane modes shape the residual form's tiles only
+        bool residual = false;
+        for (int j = 0; j < n_jobs; ++j)
+            residual |= !gram_form(jobs[j].B, jobs[j].U, jobs[j].S);
         std::vector<std::pair<float, int>> ranked;
         for (int c = 0; c < N_CHOICES; ++c) {
+            if (!residual && (choice_lane_mode(c) != 0 ||
+                              choice_policy(c) != choice_policy(DEFAULT_CHOICE)))
+                continue;
             if (run_choice(jobs, n_jobs, c, H, y, z, llr, ws, workspace_bytes, false, stream) != OCD_OK)
                 continue;
             const float ms = time_choice(c);

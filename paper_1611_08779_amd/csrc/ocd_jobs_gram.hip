@@ -1,0 +1,97 @@
+// ocd_jobs_gram.hip -- the batched launch's tiles in the Gram form (ocd_gram.h): one
+// subcarrier (and 16 of its symbols) per tile, one kernel per user bound, so that jobs
+// with few users keep the registers and occupancy of their own tile shape.
+#include "ocd_gram.h"
+#include "ocd_jobs.h"
+
+namespace ocd {
+
+template <int UP, bool S8, bool F16, bool BOX>
+__device__ __forceinline__ void job_gram_tile(const Params &P, long w, int s0, int ns, double *lds,
+                                              GramUser *us)
+{
+    switch (gram_chunk(P)) {
+    case 4: gram_tile<UP, S8, F16, BOX, true, 4>(P, w, s0, ns, lds, us); break;
+    case 2: gram_tile<UP, S8, F16, BOX, true, 2>(P, w, s0, ns, lds, us); break;
+    case 1: gram_tile<UP, S8, F16, BOX, true, 1>(P, w, s0, ns, lds, us); break;
+    default: gram_tile<UP, S8, F16, BOX, false, 1>(P, w, s0, ns, lds, us); break;
+    }
+}
+
+template <int UP, bool F16, bool BOX>
+__global__ __launch_bounds__(GRAM_THREADS, 2) void k_jobs_gram(const JobDesc *__restrict__ jobs,
+                                                               const TileDesc *__restrict__ tiles,
+                                                               unsigned int *__restrict__ next,
+                                                               int ntiles, int persistent)
+{
+    constexpr int A = GramLds<UP, false>::DOUBLES, B = GramLds<UP, true>::DOUBLES;
+    __shared__ __align__(16) double lds[A > B ? A : B];
+    __shared__ GramUser us[UP];
+    __shared__ int s_tile;
+    int ti = blockIdx.x;
+    if (persistent) {
+        if (threadIdx.x == 0) s_tile = (int)atomicAdd(next, 1u);
+        __syncthreads();
+        ti = __builtin_amdgcn_readfirstlane(s_tile);
+    }
+    while (ti < ntiles) {
+        // claim the following tile now; its value is published after this tile
+        int claimed = ntiles;
+        if (persistent && threadIdx.x == 0) claimed = (int)atomicAdd(next, 1u);
+        const TileDesc td = tiles[ti];
+        const Params P = jobs[__builtin_amdgcn_readfirstlane(td.job)].P;
+        const int v = __builtin_amdgcn_readfirstlane(td.vbase);
+        const int ns = __builtin_amdgcn_readfirstlane(td.nvb);
+        const int w = v / P.S, s0 = v - w * P.S;
+        if (P.S <= 8) job_gram_tile<UP, true, F16, BOX>(P, w, s0, ns, lds, us);
+        else job_gram_tile<UP, false, F16, BOX>(P, w, s0, ns, lds, us);
+        if (!persistent) break;
+        __syncthreads();   // this tile is done with LDS (and with s_tile)
+        if (threadIdx.x == 0) s_tile = claimed;
+        __syncthreads();
+        ti = __builtin_amdgcn_readfirstlane(s_tile);
+    }
+}
+
+template <int UP, bool F16, bool BOX>
+static hipError_t launch_jobs_k(const JobDesc *jobs, const TileDesc *tiles, unsigned int *next,
+                                int ntiles, int persistent, hipStream_t s)
+{
+    auto fn = k_jobs_gram<UP, F16, BOX>;
+    int grid = ntiles;
+    if (persistent) {
+        int per_cu = 0;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void *>(fn), GRAM_THREADS, 0);
+        if (e != hipSuccess) return e;
+        const long fit = (long)per_cu * device_cu_count();
+        if (fit >= 1 && fit < grid) grid = (int)fit;
+    }
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(GRAM_THREADS), 0, s, jobs, tiles, next, ntiles,
+                       persistent);
+    return hipGetLastError();
+}
+
+template <int UP>
+static hipError_t launch_jobs_u(bool f16, bool box, const JobDesc *jobs, const TileDesc *tiles,
+                                unsigned int *next, int ntiles, int persistent, hipStream_t s)
+{
+    if (f16) return box ? launch_jobs_k<UP, true, true>(jobs, tiles, next, ntiles, persistent, s)
+                        : launch_jobs_k<UP, true, false>(jobs, tiles, next, ntiles, persistent, s);
+    return box ? launch_jobs_k<UP, false, true>(jobs, tiles, next, ntiles, persistent, s)
+               : launch_jobs_k<UP, false, false>(jobs, tiles, next, ntiles, persistent, s);
+}
+
+hipError_t launch_jobs_gram(int which, bool f16, bool box, const JobDesc *jobs,
+                            const TileDesc *tiles, unsigned int *next, int ntiles, int persistent,
+                            hipStream_t s)
+{
+    switch (which) {
+    case 1: return launch_jobs_u<8>(f16, box, jobs, tiles, next, ntiles, persistent, s);
+    case 2: return launch_jobs_u<16>(f16, box, jobs, tiles, next, ntiles, persistent, s);
+    case 3: return launch_jobs_u<32>(f16, box, jobs, tiles, next, ntiles, persistent, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace ocd

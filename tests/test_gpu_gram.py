@@ -1,0 +1,96 @@
+"""GPU parity of the Gram form of the detection (ocd_gram.h) at the sizes where its
+tiles, antenna blocks and lane groups end: users around 8, 16 and 32, symbols around 8
+and 16, antennas around whole blocks and around the changes of its summation length,
+rows that are not 16-byte aligned, every option of the call.  Against the FP64 oracle on
+the values the GPU received, element by element, with the bars of the FP32 path."""
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_util import (LLR_TOL_F32, Z_TOL_F32, dev, from_f16_pairs, host, llr_rel_err, oracle_ref,
+                      say, to_f16_pairs, z_rel_err)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ocd():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1611_08779_amd as m
+    return m
+
+
+CASES = [
+    # B, U, W, S, Q, K, mode, storage: a tile's last user, symbol or antenna, and the next
+    (16, 8, 5, 3, 4, 3, "mmse", "f32"), (18, 9, 4, 8, 6, 2, "box", "f32"),
+    (32, 16, 3, 9, 2, 4, "mmse", "f16"), (34, 17, 3, 16, 4, 3, "box", "f32"),
+    (64, 32, 2, 17, 6, 2, "mmse", "f32"), (62, 31, 2, 8, 4, 3, "hybrid", "f16"),
+    (2, 1, 7, 3, 2, 1, "box", "f32"), (63, 4, 5, 14, 6, 3, "mmse", "f32"),
+    (65, 12, 3, 33, 4, 2, "box", "f16"), (127, 8, 4, 14, 6, 3, "mmse", "f32"),
+    (128, 8, 4, 14, 6, 3, "hybrid", "f16"), (130, 20, 3, 5, 4, 3, "box", "f32"),
+    (136, 32, 2, 15, 2, 4, "hybrid", "f32"), (264, 3, 4, 1, 4, 3, "mmse", "f32"),
+    (100, 12, 6, 1, 4, 3, "box", "f32"), (96, 24, 4, 2, 6, 3, "hybrid", "f32"),
+    (1024, 8, 2, 4, 4, 2, "mmse", "f16"), (7, 3, 300, 6, 4, 256, "mmse", "f32"),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=["-".join(map(str, c)) for c in CASES])
+def test_gram_form_edges(ocd, case):
+    B, U, W, S, Q, K, mode, storage = case
+    say("gram case", case)
+    wl = synth.make_workload(B, U, W, S, Q, 15.0, seed=[210, B, U, S])
+    N0 = float(np.float32(wl["N0"]))
+    lam, beta = None, 0.0
+    if mode == "hybrid":
+        lam = (N0 * np.linspace(0.5, 2.0, K)).astype(np.float32)
+        beta = 0.9
+    if storage == "f16":
+        H, y = to_f16_pairs(wl["H"]), to_f16_pairs(wl["y"])
+        Hr, yr = from_f16_pairs(H), from_f16_pairs(y)
+    else:
+        H, y = wl["H"], wl["y"]
+        Hr, yr = H, y
+    zo, Lo, _ = oracle_ref(Hr, yr, K, Q, mode, N0, 1.0, lam, float(np.float32(beta)))
+    lam_t = None if lam is None else dev(lam)
+
+    def shifted(a):   # the same array one entry past an aligned address
+        flat = np.concatenate([a.reshape(-1)[:a[0, 0, 0].size], a.reshape(-1)])
+        return dev(flat)[a[0, 0, 0].size:].reshape(a.shape)
+
+    for name, Ht, yt in (("aligned", dev(H), dev(y)), ("shifted", shifted(H), shifted(y))):
+        z, L, _ = ocd.detect(Ht, yt, K, Q, mode, N0, 1.0, beta, lam=lam_t, storage=storage)
+        torch.cuda.synchronize()
+        ez, el = z_rel_err(host(z), zo), llr_rel_err(host(L), Lo)
+        say("  %s z err %.3g  llr err %.3g" % (name, ez, el))
+        assert ez <= Z_TOL_F32 and el <= LLR_TOL_F32
+        z1, _, _ = ocd.detect(Ht, yt, K, Q, mode, N0, 1.0, beta, lam=lam_t, storage=storage,
+                              want_llr=False)
+        _, L1, _ = ocd.detect(Ht, yt, K, Q, mode, N0, 1.0, beta, lam=lam_t, storage=storage,
+                              want_z=False)
+        pre = ocd.preprocess(Ht, K, Q, mode, N0, lam=lam_t, storage=storage)
+        zp, Lp, _ = ocd.detect(Ht, yt, K, Q, mode, N0, 1.0, beta, lam=lam_t, storage=storage,
+                               pre=pre)
+        torch.cuda.synchronize()
+        assert torch.equal(z1, z) and torch.equal(L1, L)
+        assert torch.equal(zp, z) and torch.equal(Lp, L)
+
+
+def test_one_vector_does_not_touch_another(ocd):
+    """NaN in one receive vector stays in that vector; a zero column stays at zero."""
+    B, U, W, S, Q, K = 64, 12, 3, 14, 4, 3
+    wl = synth.make_workload(B, U, W, S, Q, 15.0, seed=[211, 0])
+    N0 = float(np.float32(wl["N0"]))
+    H, y = wl["H"].copy(), wl["y"].copy()
+    H[1, 5] = 0
+    z0, L0, _ = ocd.detect(dev(H), dev(y), K, Q, "mmse", N0)
+    y[1, 3, 7] = np.nan
+    z, L, _ = ocd.detect(dev(H), dev(y), K, Q, "mmse", N0)
+    torch.cuda.synchronize()
+    assert np.all(host(z0)[1, :, 5] == 0) and np.all(host(L0)[1, :, 5] == 0)
+    keep = np.ones((W, S), bool)
+    keep[1, 3] = False
+    assert np.array_equal(host(z)[keep], host(z0)[keep])
+    assert np.array_equal(host(L)[keep], host(L0)[keep])
+    assert np.isnan(host(z)[1, 3]).any()
