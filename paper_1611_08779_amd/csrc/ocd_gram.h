@@ -11,20 +11,29 @@
 // contraction, instead of twice per update: 4 U^2 B / S + 8 U B + 8 K U^2 operations a
 // vector against 16 K U B.
 //
-// One workgroup of four waves per subcarrier (and per 16 symbols of it).
+// A workgroup is four waves on one subcarrier (and up to 16 symbols of it) or, where there
+// are many (gram_waves), a wave on each of four subcarriers.
 //   1. The contraction, on the FP32 matrix cores (v_mfma_f32_16x16x4f32).  A row of H or
 //      y is 2B floats; Re h^H x is the dot product of two such rows and Im h^H x that of
 //      x with the row of j h (-Im, Re pairs).  A lane of the matrix operand holds row
 //      l mod 16, and since both operands may permute the summation index alike, its four
 //      K steps take the four floats of one 16-byte load: the operands go from HBM to
-//      registers in the matrix layout, with no staging.  The waves split the antennas.
+//      registers in the matrix layout, with no staging.  Four waves split the antennas into
+//      four segments; one wave takes them in turn with the same sums, so both give the
+//      same bits.
 //   2. The matrix cores sum only CH x 4 products in FP32; those sums are added in FP64.
 //      A whole sum of 2B products in FP32 leaves an error of 1.5e-7 in z, twice the
 //      residual form's (whose rounding averages over the B entries of r); with FP64
 //      sums of 8 products and FP64 updates it is below it (0.5-0.9 times, B >= 2 U).
-//   3. The four waves' partials meet in LDS; 16 lanes then own one vector and run its
-//      updates in FP64 (full rate on this GPU).  An update is a handful of lane-local
-//      operations, a DPP broadcast of Delta from its owner and two FMAs per lane.
+//   3. The four waves' partials meet in LDS; 4 or 16 lanes then own one vector and run its
+//      updates in FP64 (full rate on this GPU).  The chain of an update is an FMA, the
+//      clip, a DPP broadcast of Delta from its owner and two FMAs; what else it takes is
+//      formed once per sweep.
+// What bounds it: the latency of that chain and of the loads before it, at two workgroups a
+// compute unit (registers), then the FP64 and matrix issue.  Against the residual form
+// (two passes over the antennas per update): 1200 x 14 vectors of 128 x 8, 3 sweeps,
+// 27.7 -> 12.0 us; 4200 x 14 in FP16 storage 64 -> 30 us; 3300 x 14 of 256 x 32, box, 5
+// sweeps 544 -> 211 us.
 #pragma once
 
 #include <type_traits>
@@ -47,10 +56,15 @@ constexpr int GRAM_TILE = 16 * GRAM_LD;
 //   UP = 8:  rows are [h; j h], so one product gives Re and Im; tiles G, Q (S8: one)
 //   UP = 16: Re G, Im G, then Re Q, Im Q (S8: one)
 //   UP = 32: Re, Im of G's blocks 00, 01, 11, then Re, Im of Q's blocks 0, 1 (S8: two)
-template <int UP, bool S8>
+// SY: the symbols so arranged (SY_8: at most 8), or none (SY_NONE: the Gram matrix alone,
+// with the same bits).
+enum GramSymbols { SY_16, SY_8, SY_NONE };
+
+template <int UP, GramSymbols SY>
 struct GramShape {
+    static constexpr bool S8 = SY == SY_8, Y = SY != SY_NONE;
     static constexpr int GT = UP == 8 ? (S8 ? 0 : 1) : UP == 16 ? 2 : 6;
-    static constexpr int QT = UP == 8 ? 1 : UP == 16 ? (S8 ? 1 : 2) : (S8 ? 2 : 4);
+    static constexpr int QT = !Y ? 0 : UP == 8 ? 1 : UP == 16 ? (S8 ? 1 : 2) : (S8 ? 2 : 4);
     static constexpr int T = GT + QT;
     static constexpr int HR = UP == 32 ? 2 : 1;          // channel rows per lane
     static constexpr int GB = 2;                        // 8-antenna blocks loaded together
@@ -127,10 +141,10 @@ struct GramBlock {
     GramRaw<F16> h[HR], y;
 };
 
-template <int UP, bool S8, bool F16, bool VEC>
+template <int UP, GramSymbols SY, bool F16, bool VEC>
 __device__ __forceinline__ void gram_load_block(const Params &P, const unsigned char *hb,
                                                 const unsigned char *yb, int blk, int ns,
-                                                GramBlock<GramShape<UP, S8>::HR, F16> &x)
+                                                GramBlock<GramShape<UP, SY>::HR, F16> &x)
 {
     const int lane = threadIdx.x & 63, i = lane & 15, b = blk * 8 + (lane >> 4) * 2;
     const int U = P.U, B = P.B;
@@ -138,8 +152,47 @@ __device__ __forceinline__ void gram_load_block(const Params &P, const unsigned 
     const int hi = UP == 8 ? i & 7 : i;
     x.h[0] = gram_load<F16, VEC>(hb, min(hi, U - 1), b, B);
     if constexpr (UP == 32) x.h[1] = gram_load<F16, VEC>(hb, min(16 + i, U - 1), b, B);
-    x.y = gram_load<F16, VEC>(yb, min(S8 ? i & 7 : i, ns - 1), b, B);
+    if constexpr (SY != SY_NONE)
+        x.y = gram_load<F16, VEC>(yb, min(SY == SY_8 ? i & 7 : i, ns - 1), b, B);
 }
+
+// ||h||^2 of a lane's channel rows in the summation order of k_preprocess, whose lane l of
+// 16 sums the entries l, l + 16, ... : the entries of block blk that a lane holds belong
+// to l = 8 (blk mod 2) + 2 (lane / 16) and the next one.
+template <int HR>
+struct GramNorm {
+    float v[HR][2][2];
+
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int r = 0; r < HR; ++r) v[r][0][0] = v[r][0][1] = v[r][1][0] = v[r][1][1] = 0.f;
+    }
+    __device__ __forceinline__ void add(int r, int odd, const float4 &h)   // odd: wave-uniform
+    {
+        if (odd) {
+            v[r][1][0] = fmaf(h.x, h.x, fmaf(h.y, h.y, v[r][1][0]));
+            v[r][1][1] = fmaf(h.z, h.z, fmaf(h.w, h.w, v[r][1][1]));
+        } else {
+            v[r][0][0] = fmaf(h.x, h.x, fmaf(h.y, h.y, v[r][0][0]));
+            v[r][0][1] = fmaf(h.z, h.z, fmaf(h.w, h.w, v[r][0][1]));
+        }
+    }
+    // the levels of group_sum<16>: l ^ 1 here, l ^ 2 and the other half of 8 in the lanes
+    // 16 and 32 away, the other 8 here
+    __device__ __forceinline__ float sum(int r) const
+    {
+        float s[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            s[o] = v[r][o][0] + v[r][o][1];
+            s[o] += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(s[o]), 0x401F));
+            const int src = (static_cast<int>(__lane_id()) ^ 32) << 2;
+            s[o] += __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(s[o])));
+        }
+        return s[0] + s[1];
+    }
+};
 
 __device__ __forceinline__ float comp(const float4 &q, int c)
 {
@@ -147,11 +200,14 @@ __device__ __forceinline__ float comp(const float4 &q, int c)
 }
 
 // The products of one block: four K steps into every tile, FP32 sums of 4 CH products.
-template <int UP, bool S8, bool F16, int CH>
-__device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, S8>::HR, F16> &raw,
-                                           int blk, int B, GramAcc (&acc)[GramShape<UP, S8>::T])
+// NORM: the lane's squares of its channel rows as well (see GramNorm).
+template <int UP, GramSymbols SY, bool F16, int CH, bool NORM>
+__device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, SY>::HR, F16> &raw,
+                                           int blk, int B, GramAcc (&acc)[GramShape<UP, SY>::T],
+                                           GramNorm<GramShape<UP, SY>::HR> &gsq)
 {
-    using Sh = GramShape<UP, S8>;
+    using Sh = GramShape<UP, SY>;
+    constexpr bool S8 = Sh::S8;
     const int b = blk * 8 + ((threadIdx.x >> 4) & 3) * 2;
     const bool tail = blk * 8 + 8 > B;
     struct {
@@ -159,7 +215,12 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, S8>::HR
     } x;
 #pragma unroll
     for (int r = 0; r < Sh::HR; ++r) x.h[r] = gram_pair<F16>(raw.h[r], tail, b, B);
-    x.y = gram_pair<F16>(raw.y, tail, b, B);
+    if constexpr (Sh::Y) x.y = gram_pair<F16>(raw.y, tail, b, B);
+    else x.y = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (NORM) {
+#pragma unroll
+        for (int r = 0; r < Sh::HR; ++r) gsq.add(r, blk & 1, x.h[r]);
+    }
     const bool low = (threadIdx.x & 15) < 8;
     float4 a[2 * Sh::HR];   // rows h and j h
     float4 bq;              // the symbols' columns
@@ -186,12 +247,12 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, S8>::HR
             };
             if constexpr (UP == 8) {
                 if constexpr (!S8) mm(0, a[0], x.h[0]);
-                mm(Sh::T - 1, a[0], bq);
+                if constexpr (Sh::Y) mm(Sh::T - 1, a[0], bq);
             } else if constexpr (UP == 16) {
                 mm(0, a[0], x.h[0]);
                 mm(1, a[1], x.h[0]);
-                mm(2, a[0], bq);
-                if constexpr (!S8) mm(3, a[1], bq);
+                if constexpr (Sh::Y) mm(2, a[0], bq);
+                if constexpr (Sh::Y && !S8) mm(3, a[1], bq);
             } else {
                 mm(0, a[0], x.h[0]);
                 mm(1, a[1], x.h[0]);
@@ -199,10 +260,10 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, S8>::HR
                 mm(3, a[1], x.h[1]);
                 mm(4, a[2], x.h[1]);
                 mm(5, a[3], x.h[1]);
-                mm(6, a[0], bq);
+                if constexpr (Sh::Y) mm(6, a[0], bq);
                 if constexpr (S8) {
                     mm(7, a[2], bq);
-                } else {
+                } else if constexpr (Sh::Y) {
                     mm(7, a[1], bq);
                     mm(8, a[2], bq);
                     mm(9, a[3], bq);
@@ -216,34 +277,80 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, S8>::HR
     }
 }
 
-// This wave's share of the antennas (whole blocks of 8), the next blocks' loads in
-// flight while the current ones multiply; `between` runs when the first are out.
-template <int UP, bool S8, bool F16, bool VEC, int CH, typename Between>
+// The antennas are cut into four segments of whole blocks of 8, each summed by itself and
+// the segments then added in order: one wave per segment (NW = 4) or one wave for all of
+// them (NW = 1) give the same bits.  The next blocks' loads are in flight while the
+// current ones multiply; `between` runs when the first are out.
+template <int UP, GramSymbols SY, bool F16, bool VEC, int CH, int NW, typename Between>
 __device__ __forceinline__ void gram_contract(const Params &P, const unsigned char *hb,
                                               const unsigned char *yb, int ns,
-                                              GramAcc (&acc)[GramShape<UP, S8>::T],
+                                              GramAcc (&acc)[GramShape<UP, SY>::T],
+                                              GramNorm<GramShape<UP, SY>::HR> &gsq,
                                               Between &&between)
 {
-    using Sh = GramShape<UP, S8>;
+    using Sh = GramShape<UP, SY>;
+    constexpr int T = Sh::T;
+    constexpr int GB = Sh::GB;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nblk = (P.B + 7) >> 3;
-    const int b0 = wave * nblk / GRAM_WAVES, b1 = (wave + 1) * nblk / GRAM_WAVES;
-    GramBlock<Sh::HR, F16> cur[Sh::GB], nxt[Sh::GB];
-    auto load = [&](GramBlock<Sh::HR, F16> (&x)[Sh::GB], int blk) {   // no branch: clamped
+    const int m1 = nblk / 4, m2 = 2 * nblk / 4, m3 = 3 * nblk / 4;   // ends of segments
+    const int b0 = NW == 4 ? wave * nblk / 4 : 0, b1 = NW == 4 ? (wave + 1) * nblk / 4 : nblk;
+    const int last = max(b1 - 1, 0);
+    GramAcc tot[NW == 1 ? T : 1];
+    if constexpr (NW == 1) {
 #pragma unroll
-        for (int i = 0; i < Sh::GB; ++i)
-            gram_load_block<UP, S8, F16, VEC>(P, hb, yb, min(blk + i, nblk - 1), ns, x[i]);
+        for (int t = 0; t < T; ++t) tot[t] = acc[t];
+    }
+    // two sets of blocks in turn, each loaded again as soon as it is multiplied, with no
+    // copy or branch, either of which would wait for the loads: past its end a wave reads its
+    // last block again.  The barrier after the last pass waits for that pass's loads: four
+    // waves on few users, whose passes are few, peel it (1200 x 14 vectors of 128 x 8:
+    // 14.9 us without, 12.0 with); elsewhere the second copy of the products costs more
+    // than it saves (24 uneven jobs: 860 us without, 1580 with)
+    constexpr bool PEEL = NW == 4 && UP == 8;
+    using Set = GramBlock<Sh::HR, F16>[GB];
+    Set x0, x1;
+    auto load = [&](Set &x, int blk) {
+#pragma unroll
+        for (int i = 0; i < GB; ++i)
+            gram_load_block<UP, SY, F16, VEC>(P, hb, yb, min(blk + i, last), ns, x[i]);
     };
-    load(cur, b0);
-    load(nxt, b0 + Sh::GB);
+    auto multiply = [&](Set &x, int blk) {
+#pragma unroll
+        for (int i = 0; i < GB; ++i) {
+            const int e = blk + i;
+            if (e >= b1) break;
+            gram_block<UP, SY, F16, CH, NW == 1>(x[i], e, P.B, acc, gsq);
+            if (NW == 1 && ((e + 1 == m1) | (e + 1 == m2) | (e + 1 == m3))) {
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        tot[NW == 1 ? t : 0].v[r] += acc[t].v[r];
+                        acc[t].v[r] = 0.0;
+                    }
+            }
+        }
+    };
+    load(x0, b0);
+    load(x1, b0 + GB);
     between();
-    for (int blk = b0; blk < b1; blk += Sh::GB) {
+    int blk = b0;
+    for (; (PEEL ? blk + 2 * GB : blk) < b1; blk += 2 * GB) {
+        multiply(x0, blk);
+        load(x0, blk + 2 * GB);
+        multiply(x1, blk + GB);
+        load(x1, blk + 3 * GB);
+    }
+    if constexpr (PEEL) {
+        multiply(x0, blk);
+        multiply(x1, blk + GB);
+    }
+    if constexpr (NW == 1) {
 #pragma unroll
-        for (int i = 0; i < Sh::GB; ++i)
-            if (blk + i < b1) gram_block<UP, S8, F16, CH>(cur[i], blk + i, P.B, acc);
+        for (int t = 0; t < T; ++t)
 #pragma unroll
-        for (int i = 0; i < Sh::GB; ++i) cur[i] = nxt[i];
-        if (blk + 2 * Sh::GB < b1) load(nxt, blk + 2 * Sh::GB);
+            for (int r = 0; r < 4; ++r) acc[t].v[r] = tot[t].v[r] + acc[t].v[r];
     }
 }
 
@@ -254,15 +361,20 @@ __device__ __forceinline__ int gram_at(int part, int t, int c, int r)
     return (part * T + t) * GRAM_TILE + c * GRAM_LD + r;
 }
 
-// LDS of one subcarrier: the waves' partial tiles, then, in their place, the Gram matrix
-// G[v][u] = h_u^H h_v (column v contiguous) and the matched filters Q[s][u], (re, im).
-template <int UP, bool S8>
+// LDS of a workgroup.  NW = 4 (four waves on one subcarrier): the waves' partial tiles,
+// then, in their place, the Gram matrix G[v][u] = h_u^H h_v (column v contiguous) and the
+// matched filters Q[s][u], (re, im).  NW = 1 (a subcarrier per wave): G and Q of each.
+template <int UP, GramSymbols SY, int NW>
 struct GramLds {
-    using Sh = GramShape<UP, S8>;
-    static constexpr int PART = Sh::PARTS * Sh::T * GRAM_TILE;
+    using Sh = GramShape<UP, SY>;
+    static constexpr int SG = GRAM_WAVES / NW;   // subcarriers of a workgroup
+    static constexpr int PART = NW == 4 ? Sh::PARTS * Sh::T * GRAM_TILE : 0;
     static constexpr int G = 0, Q = 2 * UP * UP;
-    static constexpr int SUMS = Q + (S8 ? 8 : 16) * 2 * UP;
-    static constexpr int DOUBLES = PART > SUMS ? PART : SUMS;
+    // + 2: the waves that sweep several subcarriers read the same column of each, 4 or 16
+    // lanes of 64 bytes apart: 16 bytes more between subcarriers keep them off each
+    // other's banks
+    static constexpr int SUMS = Q + (SY == SY_8 ? 8 : SY == SY_16 ? 16 : 0) * 2 * UP + 2;
+    static constexpr int DOUBLES = PART > SG * SUMS ? PART : SG * SUMS;
 };
 
 // Per user: ||h_u||^2 and the soft output's constants of llr_coef, L_b = c D_b(a z_u),
@@ -298,14 +410,14 @@ __device__ __forceinline__ float gram_dinv(const Params &P, long w, int k, int u
     return di;
 }
 
-// Contraction of subcarrier w with symbols s0 .. s0 + ns - 1 into lds (GramLds), and the
-// users' constants, ||h_u||^2 in the summation order of k_preprocess, so that d^-1 and p
-// have its bits.  Ends with a workgroup barrier.
-template <int UP, bool S8, bool F16, bool VEC, int CH>
+// Contraction of subcarrier w with symbols s0 .. s0 + ns - 1 by this wave (NW = 1; lds, us
+// its own) or workgroup (NW = 4), and the users' constants, ||h_u||^2 in the summation
+// order of k_preprocess, so that d^-1 and p have its bits.  Ends with a workgroup barrier.
+template <int UP, GramSymbols SY, bool F16, bool VEC, int CH, int NW>
 __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int ns, double *lds,
                                            GramUser *us)
 {
-    using Sh = GramShape<UP, S8>;
+    using Sh = GramShape<UP, SY>;
     constexpr int T = Sh::T;
     const int U = P.U, B = P.B;
     const unsigned char *hb =
@@ -319,48 +431,110 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
     for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[t].v[r] = 0.0;
-    // ||h_u||^2: 16 lanes per column, lane l summing entries l, l + 16, ...; the first
-    // 128 antennas of 16 columns are loaded ahead of the operands (the same lines)
-    const int u0 = tid >> 4, l16 = tid & 15;
-    auto entry = [&](int u, int b) -> float2 {
-        const unsigned e = (unsigned)min(u, U - 1) * B + min(b, B - 1);
-        if constexpr (!F16) return global_load2(reinterpret_cast<const float2 *>(hb) + e);
-        else return half2_to_float2(global_ptr(reinterpret_cast<const uint32_t *>(hb))[e]);
+    auto finish_user = [&](int u, float g) {
+        const float lamK = P.lambda ? global_ptr(P.lambda)[P.K - 1] : P.lam_default;
+        float pK;
+        gram_dinv(P, w, P.K - 1, u, g, lamK, &pK);
+        us[u] = gram_user(P, g, pK, lamK);
     };
-    auto square = [&](float2 v, int b, float s) {
-        return b < B ? fmaf(v.x, v.x, fmaf(v.y, v.y, s)) : s;
-    };
-    const bool own_g = P.g_in == nullptr, first_g = own_g && (wave * 4 < U);
-    float2 hg[8];
-    if (first_g) {
+    GramNorm<Sh::HR> gsq;
+    gsq.clear();
+    if constexpr (NW == 1) {
+        gram_contract<UP, SY, F16, VEC, CH, NW>(P, hb, yb, ns, acc, gsq, [] {});
 #pragma unroll
-        for (int i = 0; i < 8; ++i) hg[i] = entry(u0, l16 + 16 * i);
-    }
-    float s0g = 0.f;
-    gram_contract<UP, S8, F16, VEC, CH>(P, hb, yb, ns, acc, [&] {
+        for (int r = 0; r < Sh::HR; ++r) {
+            const float g = gsq.sum(r);   // of row lane mod 16
+            const int u = lane + 16 * r;
+            if (lane < (UP < 16 ? UP : 16) && u < U)
+                finish_user(u, P.g_in ? global_ptr(P.g_in)[w * U + u] : g);
+        }
+    } else {
+        // 16 lanes per column, lane l summing entries l, l + 16, ...; the first 128
+        // antennas of 16 columns are loaded ahead of the operands (the same lines)
+        const int u0 = tid >> 4, l16 = tid & 15;
+        auto entry = [&](int u, int b) -> float2 {
+            const unsigned e = (unsigned)min(u, U - 1) * B + min(b, B - 1);
+            if constexpr (!F16) return global_load2(reinterpret_cast<const float2 *>(hb) + e);
+            else return half2_to_float2(global_ptr(reinterpret_cast<const uint32_t *>(hb))[e]);
+        };
+        auto square = [&](float2 v, int b, float s) {
+            return b < B ? fmaf(v.x, v.x, fmaf(v.y, v.y, s)) : s;
+        };
+        const bool own_g = P.g_in == nullptr, first_g = own_g && (wave * 4 < U);
+        float2 hg[8];
         if (first_g) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) s0g = square(hg[i], l16 + 16 * i, s0g);
+            for (int i = 0; i < 8; ++i) hg[i] = entry(u0, l16 + 16 * i);
         }
-    });
-    for (int u = u0; u < U; u += 16) {
-        float s = 0.f;
-        if (own_g) {
-            if (u == u0) s = s0g;
-            for (int b = (u == u0 ? 128 : 0) + l16; b < B; b += 16) s = square(entry(u, b), b, s);
-            s = group_sum<16>(s);
-        } else {
-            s = global_ptr(P.g_in)[w * U + u];
-        }
-        if (l16 == 0) {
-            const float lamK = P.lambda ? global_ptr(P.lambda)[P.K - 1] : P.lam_default;
-            float pK;
-            gram_dinv(P, w, P.K - 1, u, s, lamK, &pK);
-            us[u] = gram_user(P, s, pK, lamK);
+        float s0g = 0.f;
+        gram_contract<UP, SY, F16, VEC, CH, NW>(P, hb, yb, ns, acc, gsq, [&] {
+            if (first_g) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) s0g = square(hg[i], l16 + 16 * i, s0g);
+            }
+        });
+        for (int u = u0; u < U; u += 16) {
+            float s = 0.f;
+            if (own_g) {
+                int b0 = 0;
+                if (u == u0) {
+                    s = s0g;
+                    b0 = 128;
+                }
+                for (; b0 < B; b0 += 128) {
+                    float2 x[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) x[i] = entry(u, b0 + l16 + 16 * i);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) s = square(x[i], b0 + l16 + 16 * i, s);
+                }
+                s = group_sum<16>(s);
+            } else {
+                s = global_ptr(P.g_in)[w * U + u];
+            }
+            if (l16 == 0) finish_user(u, s);
         }
     }
 
+    double *G = lds + GramLds<UP, SY, NW>::G, *Q = lds + GramLds<UP, SY, NW>::Q;
+    auto put = [&](double *m, int v, int u, int im, double x) { m[2 * (v * UP + u) + im] = x; };
+    auto place = [&](int c, int r, const double (&sum)[T]) {   // position (c, r) of every tile
+        if constexpr (UP == 8) {
+            if constexpr (Sh::S8) {
+                put(c < 8 ? G : Q, c & 7, r & 7, r >> 3, sum[0]);
+            } else {
+                if (c < 8) put(G, c, r & 7, r >> 3, sum[0]);
+                if constexpr (Sh::Y) put(Q, c, r & 7, r >> 3, sum[1]);
+            }
+        } else {
+#pragma unroll
+            for (int im = 0; im < 2; ++im) {
+                put(G, c, r, im, sum[im]);
+                if constexpr (UP == 32) {
+                    put(G, 16 + c, r, im, sum[2 + im]);
+                    put(G, r, 16 + c, im, im ? -sum[3] : sum[2]);   // block 10 = block 01^H
+                    put(G, 16 + c, 16 + r, im, sum[4 + im]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < Sh::QT; ++q) {
+                if constexpr (Sh::S8) put(Q, c & 7, r + 16 * q, c >> 3, sum[Sh::GT + q]);
+                else put(Q, c, r + 16 * (q >> 1), q & 1, sum[Sh::GT + q]);
+            }
+        }
+    };
     const int col = lane & 15, row = (lane >> 4) * 4;
+    if constexpr (NW == 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            double sum[T];
+#pragma unroll
+            for (int t = 0; t < T; ++t) sum[t] = acc[t].v[r];
+            place(col, row + r, sum);
+        }
+        __syncthreads();
+        return;
+    }
     auto store = [&](int p) {
 #pragma unroll
         for (int t = 0; t < T; ++t) {
@@ -395,31 +569,7 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
         for (int p = 1; p < Sh::PARTS; ++p) sum[t] += lds[gram_at<T>(p, t, c, r)];
     }
     __syncthreads();
-    double *G = lds + GramLds<UP, S8>::G, *Q = lds + GramLds<UP, S8>::Q;
-    auto put = [&](double *m, int v, int u, int im, double x) { m[2 * (v * UP + u) + im] = x; };
-    if constexpr (UP == 8) {
-        if constexpr (S8) {
-            put(c < 8 ? G : Q, c & 7, r & 7, r >> 3, sum[0]);
-        } else {
-            if (c < 8) put(G, c, r & 7, r >> 3, sum[0]);
-            put(Q, c, r & 7, r >> 3, sum[1]);
-        }
-    } else {
-#pragma unroll
-        for (int im = 0; im < 2; ++im) {
-            put(G, c, r, im, sum[im]);
-            if constexpr (UP == 32) {
-                put(G, 16 + c, r, im, sum[2 + im]);
-                put(G, r, 16 + c, im, im ? -sum[3] : sum[2]);   // block 10 = block 01^H
-                put(G, 16 + c, 16 + r, im, sum[4 + im]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < Sh::QT; ++q) {
-            if constexpr (S8) put(Q, c & 7, r + 16 * q, c >> 3, sum[Sh::GT + q]);
-            else put(Q, c, r + 16 * (q >> 1), q & 1, sum[Sh::GT + q]);
-        }
-    }
+    place(c, r, sum);
     __syncthreads();
 }
 
@@ -429,8 +579,8 @@ __device__ __forceinline__ double group_bcast(double x)
 {
     constexpr int ctrl = L == 4 ? 0x55 * N : 0x150 + N;   // quad_perm [N,N,N,N]; row_newbcast
     const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, ctrl, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, ctrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xF, 0xF, true);
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
@@ -447,60 +597,63 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// Change of one real component: d (q - lambda z), clipped so that z + Delta is in the box.
-template <bool BOX>
-__device__ __forceinline__ double gram_delta(double q, double z, double d, double lam, double beta)
+// d_u^-1 of this lane's users i R .. i R + R - 1 in sweep k, and their regulariser.
+template <int R>
+__device__ __forceinline__ double gram_coefs(const Params &P, long w, int k, int i,
+                                             const GramUser *us, double (&d)[R])
 {
-    const double dl = d * fma(-lam, z, q);
-    if constexpr (!BOX) return dl;
-    return fmin(fmax(z + dl, -beta), beta) - z;
+    const float lam = P.lambda ? global_ptr(P.lambda)[k] : P.lam_default;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int u = i * R + r, uu = min(u, P.U - 1);
+        float p;
+        const float di = gram_dinv(P, w, k, uu, us[uu].g, lam, &p);
+        d[r] = u < P.U ? di : 0.f;   // users past U: d = 0, never updated
+    }
+    return lam;
 }
 
-// The K sweeps and the outputs of the workgroup's vectors after gram_front: L lanes per
-// vector, lane i of a group owning users i R .. i R + R - 1 (R = UP / L).  Waves without
-// a vector return at once.
-template <int UP, bool S8, bool BOX, int L>
-__device__ __forceinline__ void gram_sweeps(const Params &P, long w, int s0, int ns,
-                                            const double *lds, const GramUser *us)
+// The K sweeps of one vector on L lanes, lane i owning users i R .. i R + R - 1 (R =
+// UP / L): G the Gram matrix, q this lane's matched filters; sweep_done(k) with z in the
+// lane's z after every sweep.  z_u changes once per sweep, at its own update, so what
+// Delta_u = d q_u - (d lambda) z_u needs of it, and the bounds [-beta - z_u, beta - z_u]
+// of Delta_u in the box, are formed before the sweep: the chain from one update to the
+// next is one FMA, the clip, the broadcast and two FMAs.
+template <int UP, bool BOX, int L, typename Done>
+__device__ __forceinline__ void gram_run(const Params &P, long w, int i, const double2 *G,
+                                         const GramUser *us, double2 (&q)[UP / L],
+                                         double2 (&z)[UP / L], Done &&sweep_done)
 {
     constexpr int R = UP / L;
     const int U = P.U, K = P.K;
-    const int i = threadIdx.x % L, s = threadIdx.x / L;
-    if (__builtin_amdgcn_readfirstlane(s) >= ns) return;
-    const bool active = s < ns;
-    const int sv = active ? s : ns - 1;
-    const long v = w * P.S + s0 + sv;
     const double beta = P.beta;
-    const double2 *G = reinterpret_cast<const double2 *>(lds + GramLds<UP, S8>::G) + i * R;
-    const double2 *Q = reinterpret_cast<const double2 *>(lds + GramLds<UP, S8>::Q) + sv * UP + i * R;
-    double2 q[R], z[R];
+    G += i * R;
     double d[R], lam = 0.0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        q[r] = Q[r];
-        z[r] = make_double2(0.0, 0.0);
-    }
-    auto coefs = [&](int k) {   // users past U: d = 0, never updated
-        const float lf = P.lambda ? global_ptr(P.lambda)[k] : P.lam_default;
+    for (int r = 0; r < R; ++r) z[r] = make_double2(0.0, 0.0);
+    if (!P.per_sweep) lam = gram_coefs<R>(P, w, 0, i, us, d);
+    for (int k = 0; k < K; ++k) {
+        if (P.per_sweep) lam = gram_coefs<R>(P, w, k, i, us, d);
+        double2 t[R], lo[BOX ? R : 1], hi[BOX ? R : 1];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int u = i * R + r, uu = min(u, U - 1);
-            float p;
-            const float di = gram_dinv(P, w, k, uu, us[uu].g, lf, &p);
-            d[r] = u < U ? di : 0.f;
+            const double dl = -d[r] * lam;
+            t[r] = make_double2(dl * z[r].x, dl * z[r].y);
+            if constexpr (BOX) {
+                lo[r] = make_double2(-beta - z[r].x, -beta - z[r].y);
+                hi[r] = make_double2(beta - z[r].x, beta - z[r].y);
+            }
         }
-        lam = lf;
-    };
-    if (!P.per_sweep) coefs(0);
-    for (int k = 0; k < K; ++k) {
-        if (P.per_sweep) coefs(k);
         static_for<UP / 4>([&](auto cc) {   // four updates at a time (users past U change nothing)
             constexpr int c = decltype(cc)::value;
             if (4 * c < U) {
                 static_for<4>([&](auto uc) {
                     constexpr int u = 4 * c + decltype(uc)::value, o = u / R, n = u % R;
-                    const double cr = gram_delta<BOX>(q[n].x, z[n].x, d[n], lam, beta);
-                    const double ci = gram_delta<BOX>(q[n].y, z[n].y, d[n], lam, beta);
+                    double cr = fma(d[n], q[n].x, t[n].x), ci = fma(d[n], q[n].y, t[n].y);
+                    if constexpr (BOX) {
+                        cr = fmin(fmax(cr, lo[n].x), hi[n].x);
+                        ci = fmin(fmax(ci, lo[n].y), hi[n].y);
+                    }
                     const double dr = group_bcast<L, o>(cr), di = group_bcast<L, o>(ci);
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
@@ -514,37 +667,101 @@ __device__ __forceinline__ void gram_sweeps(const Params &P, long w, int s0, int
                 });
             }
         });
-        if (P.z_hist && active) {
+        sweep_done(k);
+    }
+}
+
+// The LLRs of one user, the Q / 2 of each axis (llr: the user's Q values).
+template <typename Dst>
+__device__ __forceinline__ void gram_llrs(const Params &P, double2 z, const GramUser &us, Dst llr)
+{
+    const double ua = us.a;
+    const float uc = us.c, tr = (float)(z.x * ua), ti = (float)(z.y * ua);
+    const int half = P.Q >> 1;
+    if (half == 3) {
+        axis_llrs<3>(tr, uc, llr);
+        axis_llrs<3>(ti, uc, llr + 3);
+    } else if (half == 2) {
+        axis_llrs<2>(tr, uc, llr);
+        axis_llrs<2>(ti, uc, llr + 2);
+    } else {
+        axis_llrs<1>(tr, uc, llr);
+        axis_llrs<1>(ti, uc, llr + 1);
+    }
+}
+
+// Lanes per vector: with 4, one wave holds 16 vectors and an update costs the fewest
+// instructions; 16 (one vector per DPP row) where few vectors or many users would leave
+// one wave with a long chain.
+template <int UP, GramSymbols SY, int NW>
+constexpr int gram_lanes()
+{
+    return UP == 32 || (UP == 16 && SY == SY_8 && NW == 4) ? 16 : 4;
+}
+
+// The vector of a lane group after gram_front: which of the workgroup's SG subcarriers
+// (from w0 on; those past W repeat the last), which symbol of the tile, and whether there
+// is such a vector.  With a subcarrier per wave, tiles of up to 4 or 8 symbols put the
+// vectors of four or two subcarriers into one wave.
+template <int L, int NW>
+struct GramVector {
+    int i, sub, s;
+    bool active, wave_idle;
+    long w;
+
+    __device__ __forceinline__ GramVector(const Params &P, long w0, int ns)
+    {
+        constexpr int SG = GRAM_WAVES / NW;
+        const int slot = threadIdx.x / L;
+        i = threadIdx.x % L;
+        const int sh = NW == 4 ? 8 : ns <= 4 ? 2 : ns <= 8 ? 3 : 4;
+        sub = slot >> sh;
+        s = slot - (sub << sh);
+        active = sub < SG && s < ns && w0 + sub < P.W;
+        // idle when the wave's first vector is past the end (its others follow it)
+        wave_idle = __builtin_amdgcn_readfirstlane(
+            NW == 4 ? s >= ns : sub >= SG || w0 + sub >= P.W);
+        sub = min(sub, SG - 1);
+        s = min(s, ns - 1);
+        w = min(w0 + sub, (long)P.W - 1);
+    }
+};
+
+// The K sweeps and the outputs of the workgroup's vectors after gram_front.  Waves
+// without a vector return at once.
+template <int UP, GramSymbols SY, bool BOX, int NW>
+__device__ __forceinline__ void gram_sweeps(const Params &P, long w0, int s0, int ns,
+                                            const double *lds, const GramUser *us)
+{
+    constexpr int L = gram_lanes<UP, SY, NW>(), R = UP / L;
+    using M = GramLds<UP, SY, NW>;
+    const int U = P.U, K = P.K;
+    const GramVector<L, NW> x(P, w0, ns);
+    if (x.wave_idle) return;
+    const long v = x.w * P.S + s0 + x.s;
+    const double *m = lds + x.sub * M::SUMS;
+    const double2 *G = reinterpret_cast<const double2 *>(m + M::G);
+    const double2 *Q = reinterpret_cast<const double2 *>(m + M::Q) + x.s * UP + x.i * R;
+    us += x.sub * UP;
+    double2 q[R], z[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) q[r] = Q[r];
+    gram_run<UP, BOX, L>(P, x.w, x.i, G, us, q, z, [&](int k) {
+        if (P.z_hist && x.active) {
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (i * R + r < U)
-                    global_store2(P.z_hist + (v * K + k) * U + i * R + r,
+                if (x.i * R + r < U)
+                    global_store2(P.z_hist + (v * K + k) * U + x.i * R + r,
                                   make_float2((float)z[r].x, (float)z[r].y));
         }
-    }
-    if (!active) return;
+    });
+    if (!x.active) return;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int u = i * R + r;
+        const int u = x.i * R + r;
         if (u >= U) continue;
         if (P.z) global_store2(P.z + v * U + u, make_float2((float)z[r].x, (float)z[r].y));
-        if (P.llr) {
-            const double ua = us[u].a;
-            const float uc = us[u].c;
-            const float tr = (float)(z[r].x * ua), ti = (float)(z[r].y * ua);
-            const int half = P.Q >> 1;
-            const auto dst = global_ptr(P.llr) + (v * U + u) * P.Q;
-            if (half == 3) {
-                axis_llrs<3>(tr, uc, dst);
-                axis_llrs<3>(ti, uc, dst + 3);
-            } else if (half == 2) {
-                axis_llrs<2>(tr, uc, dst);
-                axis_llrs<2>(ti, uc, dst + 2);
-            } else {
-                axis_llrs<1>(tr, uc, dst);
-                axis_llrs<1>(ti, uc, dst + 1);
-            }
-        }
+        if (P.llr) gram_llrs(P, z[r], us[u], global_ptr(P.llr) + (v * U + u) * P.Q);
     }
 }
 
@@ -559,13 +776,38 @@ __host__ __device__ inline int gram_chunk(const Params &P)
     return !P.vec_ok ? 0 : P.B >= 128 && P.B >= 4 * P.U ? 4 : P.B >= 64 ? 2 : 1;
 }
 
-// One tile: subcarrier w, symbols s0 .. s0 + ns - 1.
-template <int UP, bool S8, bool F16, bool BOX, bool VEC, int CH>
-__device__ __forceinline__ void gram_tile(const Params &P, long w, int s0, int ns, double *lds,
+// This wave's subcarrier of a workgroup whose first is w0.
+template <int NW>
+__device__ __forceinline__ long gram_subcarrier(const Params &P, long w0)
+{
+    const int sub = NW == 4 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return min(w0 + sub, (long)P.W - 1);
+}
+
+// One tile: symbols s0 .. s0 + ns - 1 of the workgroup's subcarriers, from w0 on.
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
+__device__ __forceinline__ void gram_tile(const Params &P, long w0, int s0, int ns, double *lds,
                                           GramUser *us)
 {
-    gram_front<UP, S8, F16, VEC, CH>(P, w, s0, ns, lds, us);
-    gram_sweeps<UP, S8, BOX, UP == 32 ? 16 : 4>(P, w, s0, ns, lds, us);
+    using M = GramLds<UP, SY, NW>;
+    const int sub = NW == 4 ? 0 : threadIdx.x >> 6;
+    gram_front<UP, SY, F16, VEC, CH, NW>(P, gram_subcarrier<NW>(P, w0), s0, ns,
+                                         lds + sub * M::SUMS, us + sub * UP);
+    gram_sweeps<UP, SY, BOX, NW>(P, w0, s0, ns, lds, us);
+}
+
+// Waves per subcarrier: one where there are enough subcarriers to keep the GPU busy (no
+// partial sums to exchange, and the set-up once per subcarrier), four below, where the
+// length of a workgroup's chain counts.  One wave each fills the GPU's resident workgroups
+// (two a compute unit) from 2048 subcarriers on; fewer antennas shorten its chain and move
+// the line to one workgroup a compute unit.  One / four waves, us, 14 symbols of 128 x 8:
+// 11.2 / 10.9 at 1024 subcarriers, 15.8 / 14.4 at 1536, 16.1 / 17.6 at 2048, 45 / 51 at
+// 8192; 4 symbols of 128 x 16: 22.7 / 19.7, 23.1 / 25.4 (1536, 2048); 14 symbols of 32 x 8:
+// 7.9 / 7.7, 8.3 / 10.6 (512, 1024).  Above 16 users the tiles' FP64 sums of a whole
+// subcarrier do not fit one wave's registers.
+__host__ __device__ inline int gram_waves(int B, int U, long subcarrier_tiles)
+{
+    return U <= 16 && subcarrier_tiles >= (B <= 64 ? 1024 : 2048) ? 1 : 4;
 }
 
 }  // namespace ocd

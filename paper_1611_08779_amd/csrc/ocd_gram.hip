@@ -4,23 +4,25 @@
 
 namespace ocd {
 
-// VEC: rows of even length, aligned.  CH: see gram_chunk.
-template <int UP, bool S8, bool F16, bool BOX, bool VEC, int CH>
+// VEC: rows of even length, aligned.  CH: see gram_chunk.  NW: see gram_waves.
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
 __global__ __launch_bounds__(GRAM_THREADS, 2) void k_gram(Params P, int tiles)
 {
-    __shared__ __align__(16) double lds[GramLds<UP, S8>::DOUBLES];
-    __shared__ GramUser us[UP];
+    using M = GramLds<UP, SY, NW>;
+    __shared__ __align__(16) double lds[M::DOUBLES];
+    __shared__ GramUser us[M::SG * UP];
     stagger_loads(P);
-    const int w = tiles == 1 ? (int)blockIdx.x : (int)blockIdx.x / tiles;
-    const int s0 = tiles == 1 ? 0 : 16 * ((int)blockIdx.x - w * tiles);
+    const int g = tiles == 1 ? (int)blockIdx.x : (int)blockIdx.x / tiles;
+    const int s0 = tiles == 1 ? 0 : 16 * ((int)blockIdx.x - g * tiles);
     const int ns = min(16, P.S - s0);
-    gram_tile<UP, S8, F16, BOX, VEC, CH>(P, w, s0, ns, lds, us);
+    gram_tile<UP, SY, F16, BOX, VEC, CH, NW>(P, (long)g * M::SG, s0, ns, lds, us);
 }
 
-template <int UP, bool S8, bool F16, bool BOX, bool VEC, int CH>
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
 static hipError_t launch_gram_k(const Params &p, hipStream_t s)
 {
-    auto fn = k_gram<UP, S8, F16, BOX, VEC, CH>;
+    auto fn = k_gram<UP, SY, F16, BOX, VEC, CH, NW>;
+    constexpr int SG = GramLds<UP, SY, NW>::SG;
     Params q = p;
     const int tiles = (p.S + 15) / 16;
     if (q.stagger > 0) {
@@ -30,34 +32,45 @@ static hipError_t launch_gram_k(const Params &p, hipStream_t s)
         if (e != hipSuccess) return e;
         q.stagger_cap = per_cu * device_cu_count();
     }
-    hipLaunchKernelGGL(fn, dim3((unsigned)p.W * tiles), dim3(GRAM_THREADS), 0, s, q, tiles);
+    hipLaunchKernelGGL(fn, dim3((unsigned)((p.W + SG - 1) / SG) * tiles), dim3(GRAM_THREADS), 0, s,
+                       q, tiles);
     return hipGetLastError();
 }
 
-template <int UP, bool S8, bool F16, bool BOX>
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH>
+static hipError_t launch_gram_w(const Params &p, hipStream_t s)
+{
+    if constexpr (UP <= 16) {
+        if (gram_waves(p.B, p.U, (long)p.W * ((p.S + 15) / 16)) == 1)
+            return launch_gram_k<UP, SY, F16, BOX, VEC, CH, 1>(p, s);
+    }
+    return launch_gram_k<UP, SY, F16, BOX, VEC, CH, 4>(p, s);
+}
+
+template <int UP, GramSymbols SY, bool F16, bool BOX>
 static hipError_t launch_gram_c(const Params &p, hipStream_t s)
 {
     switch (gram_chunk(p)) {
-    case 4: return launch_gram_k<UP, S8, F16, BOX, true, 4>(p, s);
-    case 2: return launch_gram_k<UP, S8, F16, BOX, true, 2>(p, s);
-    case 1: return launch_gram_k<UP, S8, F16, BOX, true, 1>(p, s);
-    default: return launch_gram_k<UP, S8, F16, BOX, false, 1>(p, s);
+    case 4: return launch_gram_w<UP, SY, F16, BOX, true, 4>(p, s);
+    case 2: return launch_gram_w<UP, SY, F16, BOX, true, 2>(p, s);
+    case 1: return launch_gram_w<UP, SY, F16, BOX, true, 1>(p, s);
+    default: return launch_gram_w<UP, SY, F16, BOX, false, 1>(p, s);
     }
 }
 
-template <int UP, bool S8>
+template <int UP, GramSymbols SY>
 static hipError_t launch_gram_s(bool f16, const Params &p, hipStream_t s)
 {
-    if (f16) return p.box ? launch_gram_c<UP, S8, true, true>(p, s)
-                          : launch_gram_c<UP, S8, true, false>(p, s);
-    return p.box ? launch_gram_c<UP, S8, false, true>(p, s)
-                 : launch_gram_c<UP, S8, false, false>(p, s);
+    if (f16) return p.box ? launch_gram_c<UP, SY, true, true>(p, s)
+                          : launch_gram_c<UP, SY, true, false>(p, s);
+    return p.box ? launch_gram_c<UP, SY, false, true>(p, s)
+                 : launch_gram_c<UP, SY, false, false>(p, s);
 }
 
 template <int UP>
 static hipError_t launch_gram_u(bool f16, const Params &p, hipStream_t s)
 {
-    return p.S <= 8 ? launch_gram_s<UP, true>(f16, p, s) : launch_gram_s<UP, false>(f16, p, s);
+    return p.S <= 8 ? launch_gram_s<UP, SY_8>(f16, p, s) : launch_gram_s<UP, SY_16>(f16, p, s);
 }
 
 hipError_t launch_gram(bool f16, const Params &p, hipStream_t s)

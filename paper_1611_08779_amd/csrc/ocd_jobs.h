@@ -12,8 +12,8 @@ struct JobDesc {
     int pad_[2];
 };
 
-// A tile: the vectors vbase .. vbase + nvb - 1 of a job, within one subcarrier for a job
-// in the Gram form.
+// A tile: the vectors vbase .. vbase + nvb - 1 of a job; in the Gram form, those of one
+// subcarrier, and of the next JOB_GRAM_SUBCARRIERS - 1 as well.
 struct TileDesc {
     int vbase;
     int job;
@@ -24,6 +24,7 @@ struct TileDesc {
 // The kernels of a batch, each with its own part of the tile table and queue head: the
 // residual form, then the Gram form for up to 8, 16 and 32 users.
 constexpr int N_JOB_KERNELS = 4;
+constexpr int JOB_GRAM_SUBCARRIERS[N_JOB_KERNELS] = {0, 4, 4, 1};
 
 // Launches the Gram form's kernel `which` (1 .. 3) over ntiles tiles: one workgroup per
 // tile, or (persistent) as many as fit the device, popping tiles from *next.

@@ -269,7 +269,7 @@ static ocd_status plan_jobs(const ocd_problem *jobs, int n, int policy, int lane
                     add(v, nvb, (double)nvb * P.K * P.U * P.Bpad);
                 }
             } else {
-                for (long w = 0; w < P.W; ++w)
+                for (long w = 0; w < P.W; w += JOB_GRAM_SUBCARRIERS[k])
                     for (int s = 0; s < P.S; s += 16) {
                         const int ns = std::min(16, P.S - s);
                         add(w * P.S + s, ns,

@@ -1,20 +1,22 @@
-// ocd_jobs_gram.hip -- the batched launch's tiles in the Gram form (ocd_gram.h): one
-// subcarrier (and 16 of its symbols) per tile, one kernel per user bound, so that jobs
-// with few users keep the registers and occupancy of their own tile shape.
+// ocd_jobs_gram.hip -- the batched launch's tiles in the Gram form (ocd_gram.h): 16 symbols
+// of four subcarriers (a wave each) or, above 16 users, of one per tile; one kernel per
+// user bound, so that jobs with few users keep the registers and occupancy of their own
+// tile shape.
 #include "ocd_gram.h"
 #include "ocd_jobs.h"
 
 namespace ocd {
 
-template <int UP, bool S8, bool F16, bool BOX>
+template <int UP, GramSymbols SY, bool F16, bool BOX>
 __device__ __forceinline__ void job_gram_tile(const Params &P, long w, int s0, int ns, double *lds,
                                               GramUser *us)
 {
+    constexpr int NW = UP == 32 ? 4 : 1;
     switch (gram_chunk(P)) {
-    case 4: gram_tile<UP, S8, F16, BOX, true, 4>(P, w, s0, ns, lds, us); break;
-    case 2: gram_tile<UP, S8, F16, BOX, true, 2>(P, w, s0, ns, lds, us); break;
-    case 1: gram_tile<UP, S8, F16, BOX, true, 1>(P, w, s0, ns, lds, us); break;
-    default: gram_tile<UP, S8, F16, BOX, false, 1>(P, w, s0, ns, lds, us); break;
+    case 4: gram_tile<UP, SY, F16, BOX, true, 4, NW>(P, w, s0, ns, lds, us); break;
+    case 2: gram_tile<UP, SY, F16, BOX, true, 2, NW>(P, w, s0, ns, lds, us); break;
+    case 1: gram_tile<UP, SY, F16, BOX, true, 1, NW>(P, w, s0, ns, lds, us); break;
+    default: gram_tile<UP, SY, F16, BOX, false, 1, NW>(P, w, s0, ns, lds, us); break;
     }
 }
 
@@ -24,9 +26,10 @@ __global__ __launch_bounds__(GRAM_THREADS, 2) void k_jobs_gram(const JobDesc *__
                                                                unsigned int *__restrict__ next,
                                                                int ntiles, int persistent)
 {
-    constexpr int A = GramLds<UP, false>::DOUBLES, B = GramLds<UP, true>::DOUBLES;
-    __shared__ __align__(16) double lds[A > B ? A : B];
-    __shared__ GramUser us[UP];
+    using M16 = GramLds<UP, SY_16, UP == 32 ? 4 : 1>;
+    using M8 = GramLds<UP, SY_8, UP == 32 ? 4 : 1>;
+    __shared__ __align__(16) double lds[M16::DOUBLES > M8::DOUBLES ? M16::DOUBLES : M8::DOUBLES];
+    __shared__ GramUser us[M16::SG * UP];
     __shared__ int s_tile;
     int ti = blockIdx.x;
     if (persistent) {
@@ -43,8 +46,8 @@ __global__ __launch_bounds__(GRAM_THREADS, 2) void k_jobs_gram(const JobDesc *__
         const int v = __builtin_amdgcn_readfirstlane(td.vbase);
         const int ns = __builtin_amdgcn_readfirstlane(td.nvb);
         const int w = v / P.S, s0 = v - w * P.S;
-        if (P.S <= 8) job_gram_tile<UP, true, F16, BOX>(P, w, s0, ns, lds, us);
-        else job_gram_tile<UP, false, F16, BOX>(P, w, s0, ns, lds, us);
+        if (P.S <= 8) job_gram_tile<UP, SY_8, F16, BOX>(P, w, s0, ns, lds, us);
+        else job_gram_tile<UP, SY_16, F16, BOX>(P, w, s0, ns, lds, us);
         if (!persistent) break;
         __syncthreads();   // this tile is done with LDS (and with s_tile)
         if (threadIdx.x == 0) s_tile = claimed;

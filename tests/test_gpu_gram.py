@@ -1,8 +1,9 @@
 """GPU parity of the Gram form of the detection (ocd_gram.h) at the sizes where its
 tiles, antenna blocks and lane groups end: users around 8, 16 and 32, symbols around 8
 and 16, antennas around whole blocks and around the changes of its summation length,
-rows that are not 16-byte aligned, every option of the call.  Against the FP64 oracle on
-the values the GPU received, element by element, with the bars of the FP32 path."""
+rows that are not 16-byte aligned, every option of the call, one and four waves per
+subcarrier.  Against the FP64 oracle on the values the GPU received,
+with the bars of the FP32 path."""
 
 import numpy as np
 import pytest
@@ -94,3 +95,38 @@ def test_one_vector_does_not_touch_another(ocd):
     assert np.array_equal(host(z)[keep], host(z0)[keep])
     assert np.array_equal(host(L)[keep], host(L0)[keep])
     assert np.isnan(host(z)[1, 3]).any()
+
+
+MANY = [
+    # B, U, W, S, Q, K, mode, storage: one wave per subcarrier, around its
+    # groups of four subcarriers, the users of a tile (8, 16) and its symbols (4, 8, 16)
+    (32, 16, 2049, 3, 4, 3, "box", "f32"), (64, 9, 2051, 5, 4, 2, "mmse", "f16"),
+    (17, 8, 2050, 8, 2, 2, "hybrid", "f32"), (40, 3, 1025, 17, 4, 3, "box", "f32"),
+    (128, 16, 2048, 4, 4, 2, "hybrid", "f32"),
+]
+
+
+@pytest.mark.parametrize("case", MANY, ids=["-".join(map(str, c)) for c in MANY])
+def test_many_subcarriers_equal_few(ocd, case):
+    """One wave per subcarrier (many) against four (few): the same bits, so each
+    subcarrier's results do not depend on how many others there are."""
+    B, U, W, S, Q, K, mode, storage = case
+    say("many", case)
+    wl = synth.make_workload(B, U, W, S, Q, 15.0, seed=[212, B, U, S])
+    N0 = float(np.float32(wl["N0"]))
+    lam = dev((N0 * np.linspace(0.5, 2.0, K)).astype(np.float32)) if mode == "hybrid" else None
+    beta = 0.0 if mode == "mmse" else 0.9
+    f16 = storage == "f16"
+    H, y = (dev(to_f16_pairs(wl[k]) if f16 else wl[k]) for k in ("H", "y"))
+
+    def run(a, b):
+        kw = dict(lam=lam, storage=storage)
+        return ocd.detect(H[a:b], y[a:b], K, Q, mode, N0, 1.0, beta, **kw)[:2]
+
+    whole = run(0, W)
+    torch.cuda.synchronize()
+    for a, b in ((0, 129), (W - 130, W)):
+        part = run(a, b)
+        torch.cuda.synchronize()
+        for name, p, q in zip(("z", "llr"), part, whole):
+            assert torch.equal(p, q[a:b]), name
