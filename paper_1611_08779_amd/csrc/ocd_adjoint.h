@@ -17,6 +17,16 @@ __device__ __forceinline__ float bce_grad(float L, unsigned char bit, float inv_
     return (bit ? -1.0f / (1.0f + expf(L)) : 1.0f / (1.0f + expf(-L))) * inv_n;
 }
 
+// softplus(L) - bit L, the cross-entropy of one bit with P(bit = 1) = sigmoid(L),
+// written as max(t, 0) + log(1 + e^-|L|) with t = L for bit 0 and -L for bit 1: a
+// bit that is confidently right costs the small second term alone, which the
+// subtraction softplus(L) - L would round away in FP32
+__device__ __forceinline__ float bce_term(float L, unsigned char bit)
+{
+    const float t = bit ? -L : L;
+    return fmaxf(t, 0.f) + log1pf(expf(-fabsf(L)));
+}
+
 // dLoss/dz of one user from dLoss/dLLR through L_b = rho * D_b(x), x = z/(mu sqrt(Es)),
 // and the contribution of mu(lambda_K), rho(lambda_K) to dLoss/dlambda_K.  dLoss/dLLR
 // is read from Lbar, or (Lbar null) formed from the user's bits for the mean BCE of

@@ -386,8 +386,7 @@ ocd_status run_forward(const ocd_problem *pb, const ocd_plan &pl, const void *H,
                            z, llr, z_hist, stream);
     }
     const bool f16 = pb->storage == OCD_STORE_F16;
-    // (the history feeds the adjoint, whose training step repeats the residual form's bits)
-    if (!pl.channel_in_registers && !z_hist && gram_form(pb->B, pb->U, pb->S))
+    if (!pl.channel_in_registers && gram_form(pb->B, pb->U, pb->S))
         return launch_gram(f16, P, stream) == hipSuccess ? OCD_OK : OCD_EDEVICE;
     hipError_t e = pl.channel_in_registers
                        ? launch_forward_reg(pl.lanes_per_vector, npl, P.reg_uc, f16, P, threads,
@@ -703,6 +702,15 @@ static ocd_status check_backward_args(const ocd_problem *pb, const void *H, cons
     return OCD_OK;
 }
 
+// The most workgroups of an adjoint or training step in the Gram form: as many as have
+// their partial sums in the static scratch (and at least the plan's), so that the forms
+// with and without a workspace split the work alike.
+static int gram_max_blocks(const Params &P)
+{
+    const int fit = (int)((OCD_NOALLOC_SCRATCH_BYTES - 256) / (sizeof(float) * (size_t)(P.K + 1)));
+    return std::max(fit, P.nblocks);
+}
+
 // dLoss/dLLR from dllr, or (dllr null) formed in the kernel from bits for the mean
 // binary cross-entropy of the LLRs
 static ocd_status run_backward(const ocd_problem *pb, const ocd_plan &pl, const void *H,
@@ -728,7 +736,10 @@ static ocd_status run_backward(const ocd_problem *pb, const ocd_plan &pl, const 
     P.dbeta = dbeta;
     set_vec_ok(P, pb, H, y);
     hipError_t e;
-    if (pb->W > 0) {
+    if (pb->W > 0 && gram_form(pb->B, pb->U, pb->S)) {
+        e = launch_gram_backward(pb->storage == OCD_STORE_F16, P, gram_max_blocks(P),
+                                 lds_limit_bytes(), stream);
+    } else if (pb->W > 0) {
         e = launch_backward(pl.lanes_per_vector, npl, pb->storage == OCD_STORE_F16, P, threads,
                             lds, stream);
     } else {
@@ -852,7 +863,10 @@ static ocd_status run_train(const ocd_problem *pb, Params P, int L, int npl, int
     P.loss = loss;
     set_vec_ok(P, pb, H, y);
     hipError_t e;
-    if (pb->W > 0) {
+    if (pb->W > 0 && gram_form(pb->B, pb->U, pb->S)) {
+        e = launch_gram_train(pb->storage == OCD_STORE_F16, P, gram_max_blocks(P),
+                              lds_limit_bytes(), stream);
+    } else if (pb->W > 0) {
         e = launch_train(L, npl, pb->storage == OCD_STORE_F16, P, threads, lds, stream);
     } else {
         P.nblocks = 0;   // no workgroups: zero gradients and loss

@@ -141,6 +141,10 @@ hipError_t launch_backward(int L, int NPL, bool f16, const Params &p, int thread
 hipError_t launch_forward_reg(int L, int NPL, int UC, bool f16, const Params &p,
                               int threads, hipStream_t s);
 hipError_t launch_gram(bool f16, const Params &p, hipStream_t s);
+// max_blocks: bound on the workgroups (their partial sums); limit: LDS per workgroup
+hipError_t launch_gram_train(bool f16, const Params &p, int max_blocks, size_t limit, hipStream_t s);
+hipError_t launch_gram_backward(bool f16, const Params &p, int max_blocks, size_t limit,
+                                hipStream_t s);
 hipError_t launch_mmse(int L, int NPL, bool f16, const Params &p, int threads, size_t lds,
                        hipStream_t s);
 hipError_t launch_mmse_mfma(bool f16, const Params &p, size_t lds, hipStream_t s);

@@ -2,18 +2,21 @@
 tiles, antenna blocks and lane groups end: users around 8, 16 and 32, symbols around 8
 and 16, antennas around whole blocks and around the changes of its summation length,
 rows that are not 16-byte aligned, every option of the call, one and four waves per
-subcarrier.  Against the FP64 oracle on the values the GPU received,
+subcarrier, and its gradients.  Against the FP64 oracle on the values the GPU received,
 with the bars of the FP32 path."""
 
 import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
 from gpu_util import (LLR_TOL_F32, Z_TOL_F32, dev, from_f16_pairs, host, llr_rel_err, oracle_ref,
                       say, to_f16_pairs, z_rel_err)
 
 pytestmark = pytest.mark.gpu
+
+GRAD_TOL = 1e-3
 
 
 @pytest.fixture(scope="module")
@@ -108,8 +111,8 @@ MANY = [
 
 @pytest.mark.parametrize("case", MANY, ids=["-".join(map(str, c)) for c in MANY])
 def test_many_subcarriers_equal_few(ocd, case):
-    """One wave per subcarrier (many) against four (few): the same bits, so each
-    subcarrier's results do not depend on how many others there are."""
+    """One wave per subcarrier (many) against four (few): the same bits, forward and
+    adjoint, so each subcarrier's results do not depend on how many others there are."""
     B, U, W, S, Q, K, mode, storage = case
     say("many", case)
     wl = synth.make_workload(B, U, W, S, Q, 15.0, seed=[212, B, U, S])
@@ -118,15 +121,71 @@ def test_many_subcarriers_equal_few(ocd, case):
     beta = 0.0 if mode == "mmse" else 0.9
     f16 = storage == "f16"
     H, y = (dev(to_f16_pairs(wl[k]) if f16 else wl[k]) for k in ("H", "y"))
+    g = torch.Generator().manual_seed(7)
+    dllr = torch.randn(W, S, U, Q, generator=g).cuda()
 
     def run(a, b):
         kw = dict(lam=lam, storage=storage)
-        return ocd.detect(H[a:b], y[a:b], K, Q, mode, N0, 1.0, beta, **kw)[:2]
+        z, L, zh = ocd.detect(H[a:b], y[a:b], K, Q, mode, N0, 1.0, beta, want_hist=True, **kw)
+        _, _, dy = ocd.backward(H[a:b], y[a:b], zh, dllr[a:b].contiguous(), K, Q, mode, N0, 1.0,
+                                beta, **kw)
+        return z, L, zh, dy
 
     whole = run(0, W)
     torch.cuda.synchronize()
     for a, b in ((0, 129), (W - 130, W)):
         part = run(a, b)
         torch.cuda.synchronize()
-        for name, p, q in zip(("z", "llr"), part, whole):
+        for name, p, q in zip(("z", "llr", "z_hist", "dy"), part, whole):
             assert torch.equal(p, q[a:b]), name
+
+
+GRADS = [
+    # B, U, W, S, Q, K, mode, storage
+    (16, 8, 5, 3, 4, 3, "box", "f32"), (34, 9, 6, 8, 2, 2, "mmse", "f32"),
+    (64, 16, 5, 9, 4, 3, "hybrid", "f16"), (35, 17, 3, 16, 4, 2, "hybrid", "f32"),
+    (66, 32, 2, 17, 6, 3, "box", "f32"), (63, 5, 1025, 3, 4, 2, "hybrid", "f32"),
+    (32, 12, 1027, 4, 4, 2, "box", "f32"), (272, 4, 3, 1, 4, 3, "mmse", "f16"),
+    (64, 32, 3, 2, 4, 256, "mmse", "f32"),
+]
+
+
+@pytest.mark.parametrize("case", GRADS, ids=["-".join(map(str, c)) for c in GRADS])
+def test_gram_gradients_edges(ocd, case):
+    """The training step against the two launches (z, LLRs and dy bit for bit) and dy,
+    dlambda and dbeta against the oracle's reverse mode, 1e-3 relative L2 as for the other
+    shapes."""
+    B, U, W, S, Q, K, mode, storage = case
+    say("gram gradients", case)
+    wl = synth.make_workload(B, U, W, S, Q, 10.0, seed=[213, B, U, S])
+    N0 = float(np.float32(wl["N0"]))
+    lam = (N0 * np.linspace(0.8, 1.3, K)).astype(np.float32) if mode == "hybrid" else None
+    beta = 0.0 if mode == "mmse" else float(np.float32(0.8))
+    if storage == "f16":
+        H, y = to_f16_pairs(wl["H"]), to_f16_pairs(wl["y"])
+        Hr, yr = from_f16_pairs(H), from_f16_pairs(y)
+    else:
+        H, y = wl["H"], wl["y"]
+        Hr, yr = H, y
+    H, y = dev(H), dev(y)
+    bits = torch.from_numpy(wl["bits"]).cuda()
+    kw = dict(lam=None if lam is None else dev(lam), storage=storage)
+    z2, L2, zh = ocd.detect(H, y, K, Q, mode, N0, 1.0, beta, want_hist=True, **kw)
+    dlam2, dbeta2, dy2 = ocd.backward(H, y, zh, None, K, Q, mode, N0, 1.0, beta, bits=bits, **kw)
+    loss, dlam, dbeta, dy, z, L = ocd.train_step(H, y, bits, K, Q, mode, N0, 1.0, beta,
+                                                 want_z=True, want_llr=True, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(z, z2) and torch.equal(L, L2) and torch.equal(dy, dy2)
+    Lh = host(L).astype(np.float64)
+    dllr = (1.0 / (1.0 + np.exp(-Lh)) - wl["bits"]) / Lh.size
+    dlam_o, dbeta_o, dy_o = oracle.grad(Hr, yr, dllr, K, Q, mode, N0=N0, lam=lam, beta=beta)
+    for name, a, b in (("dlam", dlam, dlam_o), ("dlam2", dlam2, dlam_o), ("dy", dy, dy_o)):
+        a, b = host(a).ravel(), np.asarray(b).ravel()
+        e = np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300)
+        say("  %s %.3g" % (name, e))
+        assert e <= GRAD_TOL, name
+    if mode != "mmse":
+        for b in (dbeta, dbeta2):
+            assert abs(float(host(b)[0]) - dbeta_o) <= GRAD_TOL * abs(dbeta_o)
+    want = np.mean(np.logaddexp(0.0, np.where(wl["bits"] != 0, -Lh, Lh)))
+    assert abs(float(host(loss)[0]) - want) <= 1e-5 * want
