@@ -106,3 +106,39 @@ def test_rejects_hybrid(ocd):
     with pytest.raises(ocd.OCDError) as ei:
         ocd.detect_fixed(dev(Hq), dev(yq), 2, 4, "hybrid", N0)
     assert ei.value.status == -2
+
+
+def _extreme_words(B, U, W, S, kind, seed):
+    """Words that leave the byte products (|h| >= 32640) or the 16-bit change of z
+    (a tiny channel against a large y), beside ordinary ones; every sum within 36 bits."""
+    g = np.random.default_rng(seed)
+    H = np.clip(np.round(1448 * g.standard_normal((W, U, B, 2))), -32768, 32767)
+    y = np.clip(np.round(2000 * g.standard_normal((W, S, B, 2))), -32768, 32767)
+    if kind == "wide":       # some subcarriers only
+        H[::2, 0, 0] = (32640, -32768)
+        H[1::3, U - 1, B - 1] = (-32768, 32767)
+        H[1, 0, 1] = (32639, -32639)
+    elif kind == "large":    # the first or a later update of some vectors
+        H[::2, U - 1] = np.round(0.05 * H[::2, U - 1])
+        y[:, S // 2] = np.where(y[:, S // 2] < 0, -32768, 32767)
+    return H.astype(np.int16), y.astype(np.int16)
+
+
+@pytest.mark.parametrize("B,U,W,S,Q,K,mode,kind", [
+    (128, 8, 6, 14, 6, 3, "mmse", "wide"), (32, 4, 5, 16, 4, 2, "box", "wide"),
+    (64, 3, 6, 5, 4, 3, "mmse", "large"), (128, 8, 5, 9, 6, 3, "mmse", "large"),
+    (200, 5, 4, 17, 4, 2, "mmse", "large"), (31, 2, 4, 33, 2, 2, "box", "plain"),
+    (33, 1, 3, 4, 6, 4, "mmse", "plain"), (65, 32, 2, 15, 4, 2, "mmse", "plain"),
+    (129, 9, 3, 8, 4, 3, "box", "plain"), (256, 32, 2, 14, 4, 2, "mmse", "plain"),
+    (130, 2, 3, 16, 2, 3, "mmse", "wide"), (257, 3, 2, 6, 4, 2, "mmse", "plain"),
+])
+def test_tiles_of_symbols(ocd, B, U, W, S, Q, K, mode, kind):
+    """The matrix-core tiles at the ends of their antenna blocks and symbols, and where
+    they leave the integer units; rows aligned and not."""
+    say("fixed tile case", B, U, W, S, Q, K, mode, kind)
+    Hq, yq = _extreme_words(B, U, W, S, kind, [74, B, U, S])
+    zg, Lg = run_fixed(ocd, Hq, yq, K, Q, mode, float(np.float32(0.3)))
+    flat = dev(np.concatenate([Hq[0, 0, 0], Hq.reshape(-1)]))
+    z, L = ocd.detect_fixed(flat[2:].reshape(Hq.shape), dev(yq), K, Q, mode, float(np.float32(0.3)))
+    torch.cuda.synchronize()
+    assert np.array_equal(host(z), zg) and np.array_equal(host(L), Lg)
