@@ -32,7 +32,7 @@
 // What bounds it: the latency of that chain and of the loads before it, at two workgroups a
 // compute unit (registers), then the FP64 and matrix issue.  Against the residual form
 // (two passes over the antennas per update): 1200 x 14 vectors of 128 x 8, 3 sweeps,
-// 27.7 -> 12.0 us; 4200 x 14 in FP16 storage 64 -> 30 us; 3300 x 14 of 256 x 32, box, 5
+// 27.7 -> 12.0 us; 4200 x 14 in FP16 storage 64 -> 27 us; 3300 x 14 of 256 x 32, box, 5
 // sweeps 544 -> 211 us.
 #pragma once
 
@@ -44,6 +44,7 @@
 namespace ocd {
 
 typedef float f32x4_acc __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int GRAM_WAVES = 4;
 constexpr int GRAM_THREADS = 64 * GRAM_WAVES;
@@ -134,6 +135,21 @@ __device__ __forceinline__ float4 pick(bool c, float4 a, float4 b)
 {
     return make_float4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
 }
+// The same on pairs stored in FP16, (re, im) in a dword.
+__device__ __forceinline__ u32x2_t times_j(u32x2_t q)
+{
+    return u32x2_t{__builtin_amdgcn_alignbit(q.x, q.x, 16) ^ 0x8000u,
+                   __builtin_amdgcn_alignbit(q.y, q.y, 16) ^ 0x8000u};
+}
+__device__ __forceinline__ u32x2_t times_mj(u32x2_t q)
+{
+    return u32x2_t{__builtin_amdgcn_alignbit(q.x, q.x, 16) ^ 0x80000000u,
+                   __builtin_amdgcn_alignbit(q.y, q.y, 16) ^ 0x80000000u};
+}
+__device__ __forceinline__ u32x2_t pick(bool c, u32x2_t a, u32x2_t b)
+{
+    return u32x2_t{c ? a.x : b.x, c ? a.y : b.y};
+}
 
 // Operands of one 8-antenna block: this lane's channel rows and its symbol row.
 template <int HR, bool F16>
@@ -199,8 +215,11 @@ __device__ __forceinline__ float comp(const float4 &q, int c)
     return c == 0 ? q.x : c == 1 ? q.y : c == 2 ? q.z : q.w;
 }
 
-// The products of one block: four K steps into every tile, FP32 sums of 4 CH products.
-// NORM: the lane's squares of its channel rows as well (see GramNorm).
+// The products of one block into every tile: four K steps, FP32 sums of 4 CH products,
+// or, for FP16 storage (CH = 4), one K step of v_mfma_f32_16x16x16_f16, whose 16 products
+// are exact in FP32 and whose sums err less than a chain of FP32 steps (3.6e-8 of the sum
+// for 16 products against 6.5e-8; the chain of 4, used where the others err too much, 3.3e-8),
+// at an eighth of the matrix time.  NORM: the lane's squares of its channel rows as well (see GramNorm).
 template <int UP, GramSymbols SY, bool F16, int CH, bool NORM>
 __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, SY>::HR, F16> &raw,
                                            int blk, int B, GramAcc (&acc)[GramShape<UP, SY>::T],
@@ -210,20 +229,33 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, SY>::HR
     constexpr bool S8 = Sh::S8;
     const int b = blk * 8 + ((threadIdx.x >> 4) & 3) * 2;
     const bool tail = blk * 8 + 8 > B;
+    using Op = typename std::conditional<F16, u32x2_t, float4>::type;
+    auto operand = [&](const GramRaw<F16> &q) -> Op {
+        if constexpr (F16) {
+            u32x2_t v = q.v;
+            if (tail) {   // the same for the whole wave
+                if (b >= B) v.x = 0;
+                if (b + 1 >= B) v.y = 0;
+            }
+            return v;
+        } else {
+            return gram_pair<F16>(q, tail, b, B);
+        }
+    };
     struct {
-        float4 h[Sh::HR], y;
+        Op h[Sh::HR], y;
     } x;
 #pragma unroll
-    for (int r = 0; r < Sh::HR; ++r) x.h[r] = gram_pair<F16>(raw.h[r], tail, b, B);
-    if constexpr (Sh::Y) x.y = gram_pair<F16>(raw.y, tail, b, B);
-    else x.y = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int r = 0; r < Sh::HR; ++r) x.h[r] = operand(raw.h[r]);
+    if constexpr (Sh::Y) x.y = operand(raw.y);
+    else x.y = Op{};
     if constexpr (NORM) {
 #pragma unroll
-        for (int r = 0; r < Sh::HR; ++r) gsq.add(r, blk & 1, x.h[r]);
+        for (int r = 0; r < Sh::HR; ++r) gsq.add(r, blk & 1, gram_pair<F16>(raw.h[r], tail, b, B));
     }
     const bool low = (threadIdx.x & 15) < 8;
-    float4 a[2 * Sh::HR];   // rows h and j h
-    float4 bq;              // the symbols' columns
+    Op a[2 * Sh::HR];   // rows h and j h
+    Op bq;              // the symbols' columns
     if constexpr (UP == 8) {
         a[0] = a[1] = pick(low, x.h[0], times_j(x.h[0]));
         bq = S8 ? pick(low, x.h[0], x.y) : x.y;
@@ -236,14 +268,20 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, SY>::HR
         bq = S8 ? pick(low, x.y, times_mj(x.y)) : x.y;
     }
     const f32x4_acc zero = {0.f, 0.f, 0.f, 0.f};
+    static_assert(!F16 || CH == 4, "one K step a block");
 #pragma unroll
     for (int c0 = 0; c0 < 4; c0 += CH) {
         f32x4_acc d[Sh::T];
 #pragma unroll
-        for (int c = c0; c < c0 + CH; ++c) {
-            auto mm = [&](int t, const float4 &p, const float4 &q) {
-                d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp(p, c), comp(q, c),
-                                                            c == c0 ? zero : d[t], 0, 0, 0);
+        for (int c = c0; c < c0 + (F16 ? 1 : CH); ++c) {
+            auto mm = [&](int t, const Op &p, const Op &q) {
+                if constexpr (F16)
+                    d[t] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, p),
+                                                                 __builtin_bit_cast(f16x4_t, q), zero,
+                                                                 0, 0, 0);
+                else
+                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp(p, c), comp(q, c),
+                                                                c == c0 ? zero : d[t], 0, 0, 0);
             };
             if constexpr (UP == 8) {
                 if constexpr (!S8) mm(0, a[0], x.h[0]);
@@ -765,15 +803,26 @@ __device__ __forceinline__ void gram_sweeps(const Params &P, long w0, int s0, in
     }
 }
 
-// How long the FP32 sums of the contraction are (CH of 4 products each; 0: rows without
-// vector loads, sums of 4): 16 products from 128 antennas and four per user on, 8 from 64
-// antennas on, 4 below, the longest whose rounding stays below the residual form's.
+// How long the FP32 sums of the contraction are (CH of 4 products each): 16 products from 128 antennas and four per user on, 8 from 64
+// antennas on, 4 below and for rows without vector loads, the longest whose rounding stays below the residual form's.
 // Error of z at 8-20 dB (residual form; 16, 8, 4 products):
 //   B = 128, U = 8:  5.7e-8; 4.6e-8, 3.7e-8, 3.3e-8     B = 64, U = 16: 8.0e-8; 8.8e-8, 6.6e-8, 5.1e-8
 //   B = 128, U = 32: 8.4e-8; 7.2e-8, 5.2e-8, 4.0e-8     B = 32, U = 16: 1.13e-7; 1.71e-7, 1.19e-7, 9.0e-8
-__host__ __device__ inline int gram_chunk(const Params &P)
+// FP16 storage takes one step of 16 products a block at any size (see gram_block).
+// f(VEC, CH) as integral constants, one return type.
+template <bool F16, typename F>
+__host__ __device__ __forceinline__ auto gram_dispatch(const Params &P, F &&f)
 {
-    return !P.vec_ok ? 0 : P.B >= 128 && P.B >= 4 * P.U ? 4 : P.B >= 64 ? 2 : 1;
+    using std::integral_constant;
+    if constexpr (F16) {
+        if (P.vec_ok) return f(std::true_type{}, integral_constant<int, 4>{});
+        return f(std::false_type{}, integral_constant<int, 4>{});
+    } else {
+        if (!P.vec_ok) return f(std::false_type{}, integral_constant<int, 1>{});
+        if (P.B >= 128 && P.B >= 4 * P.U) return f(std::true_type{}, integral_constant<int, 4>{});
+        if (P.B >= 64) return f(std::true_type{}, integral_constant<int, 2>{});
+        return f(std::true_type{}, integral_constant<int, 1>{});
+    }
 }
 
 // This wave's subcarrier of a workgroup whose first is w0.

@@ -4,7 +4,7 @@
 
 namespace ocd {
 
-// VEC: rows of even length, aligned.  CH: see gram_chunk.  NW: see gram_waves.
+// VEC: rows of even length, aligned.  CH: see gram_dispatch.  NW: see gram_waves.
 template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
 __global__ __launch_bounds__(GRAM_THREADS, 2) void k_gram(Params P, int tiles)
 {
@@ -50,12 +50,9 @@ static hipError_t launch_gram_w(const Params &p, hipStream_t s)
 template <int UP, GramSymbols SY, bool F16, bool BOX>
 static hipError_t launch_gram_c(const Params &p, hipStream_t s)
 {
-    switch (gram_chunk(p)) {
-    case 4: return launch_gram_w<UP, SY, F16, BOX, true, 4>(p, s);
-    case 2: return launch_gram_w<UP, SY, F16, BOX, true, 2>(p, s);
-    case 1: return launch_gram_w<UP, SY, F16, BOX, true, 1>(p, s);
-    default: return launch_gram_w<UP, SY, F16, BOX, false, 1>(p, s);
-    }
+    return gram_dispatch<F16>(p, [&](auto vec, auto ch) {
+        return launch_gram_w<UP, SY, F16, BOX, vec(), ch()>(p, s);
+    });
 }
 
 template <int UP, GramSymbols SY>

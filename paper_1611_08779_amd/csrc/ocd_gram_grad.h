@@ -326,12 +326,9 @@ __device__ __forceinline__ void grad_front(const Params &P, long w0, int s0, int
     const long w = gram_subcarrier<NW>(P, w0);
     lds += sub * GramLds<UP, SY, NW>::SUMS;
     us += sub * UP;
-    switch (gram_chunk(P)) {
-    case 4: gram_front<UP, SY, F16, true, 4, NW>(P, w, s0, ns, lds, us); break;
-    case 2: gram_front<UP, SY, F16, true, 2, NW>(P, w, s0, ns, lds, us); break;
-    case 1: gram_front<UP, SY, F16, true, 1, NW>(P, w, s0, ns, lds, us); break;
-    default: gram_front<UP, SY, F16, false, 1, NW>(P, w, s0, ns, lds, us); break;
-    }
+    gram_dispatch<F16>(P, [&](auto vec, auto ch) {
+        gram_front<UP, SY, F16, vec(), ch(), NW>(P, w, s0, ns, lds, us);
+    });
 }
 
 template <int UP, GramSymbols SY, bool F16, bool BOX, bool TRAIN, int NW>

@@ -12,12 +12,9 @@ __device__ __forceinline__ void job_gram_tile(const Params &P, long w, int s0, i
                                               GramUser *us)
 {
     constexpr int NW = UP == 32 ? 4 : 1;
-    switch (gram_chunk(P)) {
-    case 4: gram_tile<UP, SY, F16, BOX, true, 4, NW>(P, w, s0, ns, lds, us); break;
-    case 2: gram_tile<UP, SY, F16, BOX, true, 2, NW>(P, w, s0, ns, lds, us); break;
-    case 1: gram_tile<UP, SY, F16, BOX, true, 1, NW>(P, w, s0, ns, lds, us); break;
-    default: gram_tile<UP, SY, F16, BOX, false, 1, NW>(P, w, s0, ns, lds, us); break;
-    }
+    gram_dispatch<F16>(P, [&](auto vec, auto ch) {
+        gram_tile<UP, SY, F16, BOX, vec(), ch(), NW>(P, w, s0, ns, lds, us);
+    });
 }
 
 template <int UP, bool F16, bool BOX>
