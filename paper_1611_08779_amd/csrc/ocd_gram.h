@@ -29,11 +29,11 @@
 //      updates in FP64 (full rate on this GPU).  The chain of an update is an FMA, the
 //      clip, a DPP broadcast of Delta from its owner and two FMAs; what else it takes is
 //      formed once per sweep.
-// What bounds it: the latency of that chain and of the loads before it, at two workgroups a
-// compute unit (registers), then the FP64 and matrix issue.  Against the residual form
+// What bounds it: the latency of that chain and of the loads before it, at the workgroups
+// whose registers fit a compute unit (three above 16 users), then the FP64 and matrix issue.  Against the residual form
 // (two passes over the antennas per update): 1200 x 14 vectors of 128 x 8, 3 sweeps,
-// 27.7 -> 12.0 us; 4200 x 14 in FP16 storage 64 -> 27 us; 3300 x 14 of 256 x 32, box, 5
-// sweeps 544 -> 211 us.
+// 27.7 -> 11.8 us; 4200 x 14 in FP16 storage 64 -> 26.5 us; 3300 x 14 of 256 x 32, box, 5
+// sweeps 544 -> 193 us.
 #pragma once
 
 #include <type_traits>
@@ -68,7 +68,6 @@ struct GramShape {
     static constexpr int QT = !Y ? 0 : UP == 8 ? 1 : UP == 16 ? (S8 ? 1 : 2) : (S8 ? 2 : 4);
     static constexpr int T = GT + QT;
     static constexpr int HR = UP == 32 ? 2 : 1;          // channel rows per lane
-    static constexpr int GB = 2;                        // 8-antenna blocks loaded together
     static constexpr int PARTS = UP == 32 ? 2 : 4;       // wave partials kept in LDS
 };
 
@@ -328,7 +327,6 @@ __device__ __forceinline__ void gram_contract(const Params &P, const unsigned ch
 {
     using Sh = GramShape<UP, SY>;
     constexpr int T = Sh::T;
-    constexpr int GB = Sh::GB;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nblk = (P.B + 7) >> 3;
     const int m1 = nblk / 4, m2 = 2 * nblk / 4, m3 = 3 * nblk / 4;   // ends of segments
@@ -339,50 +337,45 @@ __device__ __forceinline__ void gram_contract(const Params &P, const unsigned ch
 #pragma unroll
         for (int t = 0; t < T; ++t) tot[t] = acc[t];
     }
-    // two sets of blocks in turn, each loaded again as soon as it is multiplied, with no
-    // copy or branch, either of which would wait for the loads: past its end a wave reads its
-    // last block again.  The barrier after the last pass waits for that pass's loads: four
-    // waves on few users, whose passes are few, peel it (1200 x 14 vectors of 128 x 8:
-    // 14.9 us without, 12.0 with); elsewhere the second copy of the products costs more
-    // than it saves (24 uneven jobs: 860 us without, 1580 with)
+    // two blocks in turn, each loaded again as soon as it is multiplied, with no copy or
+    // branch, either of which would wait for the loads: past its end a wave reads its last
+    // block again.  (Four blocks in flight take registers that are worth more as waves:
+    // 3300 x 14 vectors of 256 x 32 in 235 us, not 218, 4200 x 14 of 128 x 16 in 61, not 52.)
+    // The barrier after the last pass waits for that pass's loads: four waves on few users,
+    // whose passes are few, peel it (1200 x 14 vectors of 128 x 8: 14.9 us without, 12.0
+    // with); elsewhere the second copy of the products costs more than it saves (24 uneven
+    // jobs: 860 us without, 1580 with)
     constexpr bool PEEL = NW == 4 && UP == 8;
-    using Set = GramBlock<Sh::HR, F16>[GB];
-    Set x0, x1;
-    auto load = [&](Set &x, int blk) {
-#pragma unroll
-        for (int i = 0; i < GB; ++i)
-            gram_load_block<UP, SY, F16, VEC>(P, hb, yb, min(blk + i, last), ns, x[i]);
+    GramBlock<Sh::HR, F16> x0, x1;
+    auto load = [&](GramBlock<Sh::HR, F16> &x, int blk) {
+        gram_load_block<UP, SY, F16, VEC>(P, hb, yb, min(blk, last), ns, x);
     };
-    auto multiply = [&](Set &x, int blk) {
+    auto multiply = [&](const GramBlock<Sh::HR, F16> &x, int e) {
+        if (e >= b1) return;
+        gram_block<UP, SY, F16, CH, NW == 1>(x, e, P.B, acc, gsq);
+        if (NW == 1 && ((e + 1 == m1) | (e + 1 == m2) | (e + 1 == m3))) {
 #pragma unroll
-        for (int i = 0; i < GB; ++i) {
-            const int e = blk + i;
-            if (e >= b1) break;
-            gram_block<UP, SY, F16, CH, NW == 1>(x[i], e, P.B, acc, gsq);
-            if (NW == 1 && ((e + 1 == m1) | (e + 1 == m2) | (e + 1 == m3))) {
+            for (int t = 0; t < T; ++t)
 #pragma unroll
-                for (int t = 0; t < T; ++t)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        tot[NW == 1 ? t : 0].v[r] += acc[t].v[r];
-                        acc[t].v[r] = 0.0;
-                    }
-            }
+                for (int r = 0; r < 4; ++r) {
+                    tot[NW == 1 ? t : 0].v[r] += acc[t].v[r];
+                    acc[t].v[r] = 0.0;
+                }
         }
     };
     load(x0, b0);
-    load(x1, b0 + GB);
+    load(x1, b0 + 1);
     between();
     int blk = b0;
-    for (; (PEEL ? blk + 2 * GB : blk) < b1; blk += 2 * GB) {
+    for (; (PEEL ? blk + 2 : blk) < b1; blk += 2) {
         multiply(x0, blk);
-        load(x0, blk + 2 * GB);
-        multiply(x1, blk + GB);
-        load(x1, blk + 3 * GB);
+        load(x0, blk + 2);
+        multiply(x1, blk + 1);
+        load(x1, blk + 3);
     }
     if constexpr (PEEL) {
         multiply(x0, blk);
-        multiply(x1, blk + GB);
+        multiply(x1, blk + 1);
     }
     if constexpr (NW == 1) {
 #pragma unroll
@@ -611,15 +604,21 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
     __syncthreads();
 }
 
-// The value of lane N of every aligned group of L = 4 or 16 lanes.
+// The value of lane N of every aligned group of L = 4, 8 or 16 lanes: quad_perm [N,N,N,N],
+// or row_newbcast, the one DPP move that takes both halves of a double at once.
 template <int L, int N>
 __device__ __forceinline__ double group_bcast(double x)
 {
-    constexpr int ctrl = L == 4 ? 0x55 * N : 0x150 + N;   // quad_perm [N,N,N,N]; row_newbcast
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, ctrl, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), ctrl, 0xF, 0xF, true);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+    if constexpr (L == 4) {
+        const long long b = __double_as_longlong(x);
+        const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)b, 0x55 * N, 0xF, 0xF, true);
+        const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x55 * N, 0xF, 0xF, true);
+        return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+    } else {
+        double y = __builtin_amdgcn_mov_dpp(x, 0x150 + N, 0xF, 0xF, true);
+        if constexpr (L == 8) y = __builtin_amdgcn_update_dpp(y, x, 0x158 + N, 0xF, 0xC, false);
+        return y;
+    }
 }
 
 template <typename F, int... I>
@@ -847,13 +846,12 @@ __device__ __forceinline__ void gram_tile(const Params &P, long w0, int s0, int 
 
 // Waves per subcarrier: one where there are enough subcarriers to keep the GPU busy (no
 // partial sums to exchange, and the set-up once per subcarrier), four below, where the
-// length of a workgroup's chain counts.  One wave each fills the GPU's resident workgroups
-// (two a compute unit) from 2048 subcarriers on; fewer antennas shorten its chain and move
-// the line to one workgroup a compute unit.  One / four waves, us, 14 symbols of 128 x 8:
-// 11.2 / 10.9 at 1024 subcarriers, 15.8 / 14.4 at 1536, 16.1 / 17.6 at 2048, 45 / 51 at
-// 8192; 4 symbols of 128 x 16: 22.7 / 19.7, 23.1 / 25.4 (1536, 2048); 14 symbols of 32 x 8:
-// 7.9 / 7.7, 8.3 / 10.6 (512, 1024).  Above 16 users the tiles' FP64 sums of a whole
-// subcarrier do not fit one wave's registers.
+// length of a workgroup's chain counts.  One wave each gives every SIMD two waves from 2048
+// subcarriers on; fewer antennas shorten its chain and move the line to one.  One / four
+// waves, us, 14 symbols of 128 x 8: 10.9 / 10.4 at 1024 subcarriers, 15.0 / 13.7 at 1536,
+// 15.5 / 17.3 at 2048, 45 / 51 at 8192; 4 symbols of 128 x 16: 21.8 / 19.0, 22.3 / 22.4
+// (1536, 2048); 14 symbols of 32 x 8: 7.7 / 6.9, 8.1 / 8.5 (512, 1024).  Above 16 users the
+// tiles' FP64 sums of a whole subcarrier do not fit one wave's registers.
 __host__ __device__ inline int gram_waves(int B, int U, long subcarrier_tiles)
 {
     return U <= 16 && subcarrier_tiles >= (B <= 64 ? 1024 : 2048) ? 1 : 4;

@@ -6,7 +6,7 @@ namespace ocd {
 
 // VEC: rows of even length, aligned.  CH: see gram_dispatch.  NW: see gram_waves.
 template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
-__global__ __launch_bounds__(GRAM_THREADS, 2) void k_gram(Params P, int tiles)
+__global__ __launch_bounds__(GRAM_THREADS, UP == 32 ? 3 : 2) void k_gram(Params P, int tiles)
 {
     using M = GramLds<UP, SY, NW>;
     __shared__ __align__(16) double lds[M::DOUBLES];

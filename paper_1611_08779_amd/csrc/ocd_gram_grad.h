@@ -20,10 +20,10 @@
 
 namespace ocd {
 
-// Subcarriers from which one wave takes each (see gram_waves).  Training step, one / four
-// waves, us: 4 symbols of 128 x 16 41 / 31 at 512, 44 / 54 at 1024; 14 of 128 x 8 35 / 28
-// and 38 / 50; 14 of 32 x 8 31 / 27 and 33 / 47.
-constexpr int GRAD_ONE_WAVE = 768;
+// Subcarriers from which one wave takes each (see gram_waves): one workgroup a compute unit.
+// Training step, one / four waves, us: 4 symbols of 128 x 16 38 / 28 at 512, 41 / 38 at 1024,
+// 49 / 56 at 1536; 14 of 128 x 8 31 / 26, 34 / 36, 41 / 54; 14 of 100 x 12 49 / 34, 52 / 62.
+constexpr int GRAD_ONE_WAVE = 1024;
 
 // Dynamic LDS of a launch: the contraction, the users' constants, A, the partial sums and
 // (training step) z after every sweep, for SG subcarriers of up to tsyms symbols.
@@ -331,7 +331,9 @@ __device__ __forceinline__ void grad_front(const Params &P, long w0, int s0, int
     });
 }
 
-template <int UP, GramSymbols SY, bool F16, bool BOX, bool TRAIN, int NW>
+// LOOP: more tiles than workgroups.  Without the loop the values that it would keep across
+// tiles free registers.
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool TRAIN, int NW, bool LOOP>
 __global__ __launch_bounds__(GRAM_THREADS, 2) void k_gram_grad(Params P, int tsyms, int ntiles)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -346,7 +348,7 @@ __global__ __launch_bounds__(GRAM_THREADS, 2) void k_gram_grad(Params P, int tsy
     for (int e = lane; e < K + 2; e += 64) part[e * GRAM_WAVES + wave] = 0.0;
     stagger_loads(P);
     const int per = (P.S + tsyms - 1) / tsyms;   // tiles per group of subcarriers
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    auto tile = [&](int t) {
         const int g = per == 1 ? t : t / per, s0 = (t - g * per) * tsyms;
         const int ns = min(tsyms, P.S - s0);
         const long w0 = (long)g * M::SG;
@@ -360,7 +362,14 @@ __global__ __launch_bounds__(GRAM_THREADS, 2) void k_gram_grad(Params P, int tsy
         grad_reverse<UP, SY, BOX, TRAIN, NW>(P, w0, s0, ns, tsyms, lds, us, A, part, zh);
         __syncthreads();
         if (P.dy) grad_dy<UP, F16, NW>(P, w0, s0, ns, tsyms, A);
-        __syncthreads();   // the next tile reuses the LDS
+    };
+    if constexpr (LOOP) {
+        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+            tile(t);
+            __syncthreads();   // the next tile reuses the LDS
+        }
+    } else {
+        tile(blockIdx.x);
     }
     __syncthreads();
     float *out = P.partials + (size_t)blockIdx.x * E;
@@ -390,9 +399,12 @@ template <int UP, GramSymbols SY, bool F16, bool BOX, bool TRAIN, int NW>
 static hipError_t launch_grad_k(const Params &p, int max_blocks, size_t limit, hipStream_t s)
 {
     using M = GradLds<UP, SY, TRAIN, NW>;
-    auto fn = k_gram_grad<UP, SY, F16, BOX, TRAIN, NW>;
     const int tsyms = grad_tile_symbols<UP, SY, TRAIN, NW>(p, limit);
     if (!tsyms) return hipErrorInvalidValue;
+    const int ntiles = (p.W + M::SG - 1) / M::SG * ((p.S + tsyms - 1) / tsyms);
+    const int grid = ntiles < max_blocks ? ntiles : max_blocks;
+    auto fn = grid < ntiles ? k_gram_grad<UP, SY, F16, BOX, TRAIN, NW, true>
+                            : k_gram_grad<UP, SY, F16, BOX, TRAIN, NW, false>;
     const size_t lds = M::bytes(tsyms, p.K, p.U);
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
@@ -407,8 +419,6 @@ static hipError_t launch_grad_k(const Params &p, int max_blocks, size_t limit, h
         if (e != hipSuccess) return e;
         q.stagger_cap = per_cu * device_cu_count();
     }
-    const int ntiles = (p.W + M::SG - 1) / M::SG * ((p.S + tsyms - 1) / tsyms);
-    const int grid = ntiles < max_blocks ? ntiles : max_blocks;
     hipLaunchKernelGGL(fn, dim3(grid), dim3(GRAM_THREADS), lds, s, q, tsyms, ntiles);
     return hipGetLastError();
 }

@@ -17,27 +17,19 @@ __device__ __forceinline__ void job_gram_tile(const Params &P, long w, int s0, i
     });
 }
 
-template <int UP, bool F16, bool BOX>
-__global__ __launch_bounds__(GRAM_THREADS, 2) void k_jobs_gram(const JobDesc *__restrict__ jobs,
-                                                               const TileDesc *__restrict__ tiles,
-                                                               unsigned int *__restrict__ next,
-                                                               int ntiles, int persistent)
+// A workgroup's next tile comes from the queue (PERSISTENT) or its block index: two kernels,
+// as the loop over tiles keeps values of every variant of a tile in registers, and without
+// it three workgroups fit a compute unit above 16 users, not two.
+template <int UP, bool F16, bool BOX, bool PERSISTENT>
+__global__ __launch_bounds__(GRAM_THREADS, PERSISTENT || UP < 32 ? 2 : 3) void k_jobs_gram(
+    const JobDesc *__restrict__ jobs, const TileDesc *__restrict__ tiles,
+    unsigned int *__restrict__ next, int ntiles)
 {
     using M16 = GramLds<UP, SY_16, UP == 32 ? 4 : 1>;
     using M8 = GramLds<UP, SY_8, UP == 32 ? 4 : 1>;
     __shared__ __align__(16) double lds[M16::DOUBLES > M8::DOUBLES ? M16::DOUBLES : M8::DOUBLES];
     __shared__ GramUser us[M16::SG * UP];
-    __shared__ int s_tile;
-    int ti = blockIdx.x;
-    if (persistent) {
-        if (threadIdx.x == 0) s_tile = (int)atomicAdd(next, 1u);
-        __syncthreads();
-        ti = __builtin_amdgcn_readfirstlane(s_tile);
-    }
-    while (ti < ntiles) {
-        // claim the following tile now; its value is published after this tile
-        int claimed = ntiles;
-        if (persistent && threadIdx.x == 0) claimed = (int)atomicAdd(next, 1u);
+    auto run = [&](int ti) {
         const TileDesc td = tiles[ti];
         const Params P = jobs[__builtin_amdgcn_readfirstlane(td.job)].P;
         const int v = __builtin_amdgcn_readfirstlane(td.vbase);
@@ -45,11 +37,24 @@ __global__ __launch_bounds__(GRAM_THREADS, 2) void k_jobs_gram(const JobDesc *__
         const int w = v / P.S, s0 = v - w * P.S;
         if (P.S <= 8) job_gram_tile<UP, SY_8, F16, BOX>(P, w, s0, ns, lds, us);
         else job_gram_tile<UP, SY_16, F16, BOX>(P, w, s0, ns, lds, us);
-        if (!persistent) break;
-        __syncthreads();   // this tile is done with LDS (and with s_tile)
-        if (threadIdx.x == 0) s_tile = claimed;
+    };
+    if constexpr (PERSISTENT) {
+        __shared__ int s_tile;
+        if (threadIdx.x == 0) s_tile = (int)atomicAdd(next, 1u);
         __syncthreads();
-        ti = __builtin_amdgcn_readfirstlane(s_tile);
+        int ti = __builtin_amdgcn_readfirstlane(s_tile);
+        while (ti < ntiles) {
+            // claim the following tile now; its value is published after this tile
+            int claimed = ntiles;
+            if (threadIdx.x == 0) claimed = (int)atomicAdd(next, 1u);
+            run(ti);
+            __syncthreads();   // this tile is done with LDS (and with s_tile)
+            if (threadIdx.x == 0) s_tile = claimed;
+            __syncthreads();
+            ti = __builtin_amdgcn_readfirstlane(s_tile);
+        }
+    } else {
+        if ((int)blockIdx.x < ntiles) run(blockIdx.x);
     }
 }
 
@@ -57,18 +62,19 @@ template <int UP, bool F16, bool BOX>
 static hipError_t launch_jobs_k(const JobDesc *jobs, const TileDesc *tiles, unsigned int *next,
                                 int ntiles, int persistent, hipStream_t s)
 {
-    auto fn = k_jobs_gram<UP, F16, BOX>;
-    int grid = ntiles;
-    if (persistent) {
-        int per_cu = 0;
-        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void *>(fn), GRAM_THREADS, 0);
-        if (e != hipSuccess) return e;
-        const long fit = (long)per_cu * device_cu_count();
-        if (fit >= 1 && fit < grid) grid = (int)fit;
+    if (!persistent) {
+        hipLaunchKernelGGL((k_jobs_gram<UP, F16, BOX, false>), dim3(ntiles), dim3(GRAM_THREADS), 0, s,
+                           jobs, tiles, next, ntiles);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(GRAM_THREADS), 0, s, jobs, tiles, next, ntiles,
-                       persistent);
+    auto fn = k_jobs_gram<UP, F16, BOX, true>;
+    int per_cu = 0, grid = ntiles;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per_cu, reinterpret_cast<const void *>(fn), GRAM_THREADS, 0);
+    if (e != hipSuccess) return e;
+    const long fit = (long)per_cu * device_cu_count();
+    if (fit >= 1 && fit < grid) grid = (int)fit;
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(GRAM_THREADS), 0, s, jobs, tiles, next, ntiles);
     return hipGetLastError();
 }
 
