@@ -45,26 +45,61 @@ struct GradLds {
 };
 
 // dLoss/dz of one user (z after the last sweep) through the soft output, and its
-// contribution to dLoss/dlambda_K.
-__device__ __forceinline__ float2 gram_seed(const Params &P, float2 z, float g, float d, float p,
-                                            float lamK, long o, float &lamK_bar)
+// contribution to dLoss/dlambda_K.  In the units of gram_llrs an LLR is c D_b(t), t = a z
+// and D_b(t) = (t - l0)^2 - (t - l1)^2 for the nearest levels l0, l1 with the bit 0 and 1,
+// so both derivatives are sums over the bits of dLoss/dL_b times l1 - l0 and D_b.  The sums
+// are in FP64: what lambda_K does through the soft output and through the last sweep nearly
+// cancel, and an FP32 rounding of a constant would be common to all terms.
+template <int HALF>
+__device__ __forceinline__ void gram_axis_seed(const Params &P, const GramUser &user, double t, long o,
+                                               double &sum_l, double &sum_d)
 {
-    float2 zbar = make_float2(0.f, 0.f);
-    float mu, rho;
-    gain_sinr(P, lamK, g, p, &mu, &rho);
-    if (!(rho > 0.f && mu > 0.f)) return zbar;
-    const float s = 1.0f / (mu * P.sqEs), in = P.inv_nbits, sc = P.qscale;
-    const float *Lbar = P.dllr ? P.dllr + o : nullptr;
-    const unsigned char *bt = P.dllr ? nullptr : P.bits + o;
-    float dmu = 0.f, drho = 0.f;
-    if (P.Q == 2) user_llr_adjoint<1>(Lbar, bt, in, z.x * s, z.y * s, s, mu, rho, sc, &zbar, &dmu, &drho);
-    else if (P.Q == 4) user_llr_adjoint<2>(Lbar, bt, in, z.x * s, z.y * s, s, mu, rho, sc, &zbar, &dmu, &drho);
-    else user_llr_adjoint<3>(Lbar, bt, in, z.x * s, z.y * s, s, mu, rho, sc, &zbar, &dmu, &drho);
-    if (lamK > 0.f) {
-        lamK_bar = fmaf(drho, -g / (lamK * lamK), lamK_bar);
-        lamK_bar = fmaf(dmu, -g * d * d, lamK_bar);
+    constexpr int M = 1 << HALF;
+    const float tf = (float)t;
+    sum_l = sum_d = 0.0;
+#pragma unroll
+    for (int b = 0; b < HALF; ++b) {
+        float d0 = INFINITY, d1 = INFINITY, l0 = 0.f, l1 = 0.f;
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const float l = (float)(2 * m - M + 1), d = (tf - l) * (tf - l);
+            if (((m ^ (m >> 1)) >> (HALF - 1 - b)) & 1) {
+                if (d < d1) { d1 = d; l1 = l; }
+            } else {
+                if (d < d0) { d0 = d; l0 = l; }
+            }
+        }
+        const double dl = 2.0 * (double)(l1 - l0), D = fma(t, dl, (double)(l0 * l0 - l1 * l1));
+        const float g = P.dllr ? global_ptr(P.dllr)[o + b]
+                               : bce_grad((float)(user.c * D), global_ptr(P.bits)[o + b], P.inv_nbits);
+        sum_l = fma((double)g, dl, sum_l);
+        sum_d = fma((double)g, D, sum_d);
     }
-    return zbar;
+}
+
+__device__ __forceinline__ float2 gram_seed(const Params &P, float2 z, const GramUser &user, float d,
+                                            float p, float lamK, long o, double &lamK_bar)
+{
+    if (!(user.c > 0.f)) return make_float2(0.f, 0.f);   // a zero column
+    const double tr = user.a * z.x, ti = user.a * z.y;
+    double lr, li, dr, di;   // sums over the bits of Re and Im
+    if (P.Q == 2) {
+        gram_axis_seed<1>(P, user, tr, o, lr, dr);
+        gram_axis_seed<1>(P, user, ti, o + 1, li, di);
+    } else if (P.Q == 4) {
+        gram_axis_seed<2>(P, user, tr, o, lr, dr);
+        gram_axis_seed<2>(P, user, ti, o + 2, li, di);
+    } else {
+        gram_axis_seed<3>(P, user, tr, o, lr, dr);
+        gram_axis_seed<3>(P, user, ti, o + 3, li, di);
+    }
+    if (lamK > 0.f) {   // through rho = g / lambda and mu = p (t goes with 1 / mu)
+        const double g = user.g, il = 1.0 / (double)lamK;
+        lamK_bar = fma(P.llr_c * (dr + di), -g * il * il, lamK_bar);
+        lamK_bar = fma(-(double)user.c * (tr * lr + ti * li), -g * d * ((double)d / p), lamK_bar);
+    }
+    const double s = user.c * user.a;
+    return make_float2((float)(s * lr), (float)(s * li));
 }
 
 template <int UP, GramSymbols SY, int NW>
@@ -122,7 +157,8 @@ __device__ __forceinline__ void grad_seeds(const Params &P, long w0, int s0, int
     const int U = P.U, K = P.K;
     const float lamK = P.lambda ? global_ptr(P.lambda)[K - 1] : P.lam_default;
     const int items = M::SG * ns * UP;
-    float loss = 0.f, lamK_bar = 0.f;
+    float loss = 0.f;
+    double lamK_bar = 0.0;
     for (int idx = threadIdx.x; idx < items; idx += GRAM_THREADS) {
         const int u = idx % UP, vec = idx / UP, sub = vec / ns, s = vec - sub * ns;
         const long w = w0 + sub, v = w * P.S + s0 + s, o = (v * U + u) * P.Q;
@@ -148,11 +184,11 @@ __device__ __forceinline__ void grad_seeds(const Params &P, long w0, int s0, int
             }
             float p;
             const float d = gram_dinv(P, w, K - 1, u, user.g, lamK, &p);
-            seed = gram_seed(P, z, user.g, d, p, lamK, o, lamK_bar);
+            seed = gram_seed(P, z, user, d, p, lamK, o, lamK_bar);
         }
         A[(sub * tsyms + s) * UP + u] = seed;
     }
-    add_part(part, K - 1, lamK_bar);
+    add_part(part, K - 1, (float)lamK_bar);
     if constexpr (TRAIN) add_part(part, K + 1, loss);
 }
 
