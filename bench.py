@@ -59,6 +59,21 @@ def algorithmic(B, U, S, K, Q, cbytes=8):
     return flops, nbytes
 
 
+def gram_form(B, U, S):
+    """The shapes that the library detects in the Gram form (U-long updates through
+    H^H H) rather than with two B-long passes per update."""
+    return B >= 2 * U and (U > 8 or S >= 3 or B > 256)
+
+
+def executed_flops(B, U, S, K):
+    """Real flops per vector of the form the library runs, 8 per complex MAC: the Gram
+    matrix's upper triangle shared by S symbols, the matched filters U B and K U updates
+    of U entries; else the two B-long passes per update of algorithmic()."""
+    if not gram_form(B, U, S):
+        return algorithmic(B, U, S, K, 2)[0]
+    return 4.0 * U * (U + 1) * B / S + 8.0 * U * B + 8.0 * K * U * U
+
+
 def algorithmic_mmse(B, U, S, Q, cbytes=8):
     """Per-vector work of explicit MMSE detection (Sections II-B, II-E), in real
     flops (8 per complex MAC): the Gram matrix's upper triangle U(U+1)/2 B and the
@@ -70,7 +85,7 @@ def algorithmic_mmse(B, U, S, Q, cbytes=8):
 
 
 # the sources the one-problem detection kernel and its launch are built from
-FORWARD_SOURCES = ("ocd_api.hip", "ocd_forward.hip", "ocd_tile.h", "ocd_stage.h", "ocd_device.h",
+FORWARD_SOURCES = ("ocd_api.hip", "ocd_gram.hip", "ocd_gram.h", "ocd_stage.h", "ocd_device.h",
                    "ocd_internal.h")
 
 
@@ -358,7 +373,7 @@ def summarize_profile(dirs, traffic_out, command, plan=None):
             med = statistics.median(v)
             out.append("  %-58s grid=%-8d wg=%-4d n=%-4d median=%.1f KiB  scaled=%.3f MB" % (
                 name[:58], grid, wg, len(v), med, med * 1024 * (scale or 0) / 1e6))
-            if "k_forward" in name:
+            if "k_forward" in name or "k_gram<" in name:
                 traffic.setdefault(cname, []).append((len(v), name, grid, wg, med, scale))
     for (name, grid, wg), c in sorted(per_kernel.items()):
         if "SQ_INSTS_VALU" not in c or "SQ_WAVES" not in c or not c["SQ_WAVES"]:
@@ -559,7 +574,8 @@ def main():
     t_kernel = t_step
     nvec = W * S
     bits_per_step = nvec * U * Q
-    flops_v, bytes_v = algorithmic(B, U, S, K, Q)
+    residual_flops_v, bytes_v = algorithmic(B, U, S, K, Q)
+    flops_v = executed_flops(B, U, S, K)
     value = bits_per_step / t_step / 1e9
     hbm_gbps = bytes_v * nvec / t_step / 1e9
     ach_tflops = flops_v * nvec / t_kernel / 1e12
@@ -585,7 +601,9 @@ def main():
     ber = float(torch.mean(((outs[0][1] > 0).to(torch.uint8) != slots[0]["bits"]).float()).item())
 
     npl = max(2, 1 << math.ceil(math.log2(max(2, math.ceil(B / plan.lanes_per_vector)))))
-    if plan.channel_in_registers:
+    if not plan.channel_in_registers and gram_form(B, U, S):
+        fwd_kernel = "ocd::k_gram<8, SY_16, false, false, true, 4, 4>"
+    elif plan.channel_in_registers:
         fwd_kernel = "ocd::k_forward_reg<%d, %d, 8, false, false>" % (plan.lanes_per_vector, npl)
     else:
         # the instantiation the launcher picks: unrolled users for U = 8 or 16, their
@@ -619,18 +637,20 @@ def main():
         "hbm_frac": hbm_gbps / HBM_PEAK_GBPS,
         "hbm_GBps_algorithmic": hbm_gbps,
         "roofline": {
-            "bound": "alu",
+            "bound": "hbm",
             "kernel": fwd_kernel,
-            "achieved": ach_tflops,
-            "peak": FP32_VECTOR_PEAK_TFLOPS,
-            "unit": "TFLOP/s",
-            "frac": ach_tflops / FP32_VECTOR_PEAK_TFLOPS,
-            "frac_of_nonpacked_fp32": ach_tflops / FP32_NONPACKED_TFLOPS,
+            "achieved": hbm_gbps,
+            "peak": HBM_PEAK_GBPS,
+            "unit": "GB/s",
+            "frac": hbm_gbps / HBM_PEAK_GBPS,
+            "executed_TFLOPs": ach_tflops,
+            "executed_frac_of_fp32_vector_peak": ach_tflops / FP32_VECTOR_PEAK_TFLOPS,
             "traffic": traffic,
             "avg_kernel_us": t_kernel * 1e6,
             "avg_kernel_us_source": "HIP events around the timed graph replays / launches",
             "single_eager_launch_us": t_single * 1e6,
             "flops_per_vector": flops_v,
+            "flops_per_vector_residual_form": residual_flops_v,
             "bytes_per_vector": bytes_v,
             "vectors_per_launch": nvec,
             "hbm_achieved_GBps": bytes_v * nvec / t_kernel / 1e9,
@@ -714,7 +734,7 @@ def fixed_form(torch, ocd, dev, args, slots, pb32, t_ocd, errs_ocd, nbits):
                for i in range(len(slots)))
     return {"gbps": W * S * U * Q / t / 1e9, "ms_per_step": t * 1e3, "eager_launch_us": tk * 1e6,
             "slowdown_vs_fp32": t / t_ocd, "bit_errors_fixed": errs, "bit_errors_fp32": errs_ocd,
-            "bits": nbits, "kernel": "ocd::k_forward_fx<16, 8, true>",
+            "bits": nbits, "kernel": "ocd::k_fixed_tile<2, 2>",
             "inputs": "Q5.11 int16 pairs of sqrt(B) H and sqrt(B) y, N0 B"}
 
 
@@ -949,7 +969,7 @@ def fwd_bwd_form(torch, np, ocd, synth, dev):
     tfb, _ = time_graph(torch, GraphedSteps(torch, [fwd_bwd_fused] * 8), 400, 16)
     tfb2, _ = time_graph(torch, GraphedSteps(torch, [fwd_bwd] * 8), 400, 16)
     tf, _ = time_graph(torch, GraphedSteps(torch, [fwd_only] * 8), 400, 16)
-    fl, _ = algorithmic(B5, U5, S5, K5, Q5)
+    fl = executed_flops(B5, U5, S5, K5)
     return {
         "vectors_per_s": W5 * S5 / tts, "ms_per_step": tts * 1e3,
         "step": "one launch of ocd_detect_train_bce: detection, mean BCE of the LLRs, "
@@ -1031,7 +1051,7 @@ def jobs_form(torch, np, ocd, synth, dev):
     t_eager = e0.elapsed_time(e1) / reps
     agree = all(torch.allclose(z[j], zs[j], rtol=1e-5, atol=1e-6) for j in range(len(probs)))
     total_bits = sum(p.W * p.S * p.U * p.Q for p in probs)
-    total_flops = sum(algorithmic(p.B, p.U, p.S, p.K, p.Q)[0] * p.W * p.S for p in probs)
+    total_flops = sum(executed_flops(p.B, p.U, p.S, p.K) * p.W * p.S for p in probs)
     res = {
         "ms_one_launch_graph": t_batched, "ms_one_launch_eager": t_batched_eager,
         "ms_per_job_launches_graph": t_sep,

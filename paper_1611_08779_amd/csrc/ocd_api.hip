@@ -932,6 +932,13 @@ extern "C" ocd_status ocd_autotune_train(const ocd_problem *pb, const void *H, c
                 if (train_params(pb, pl, lambda, P, npl, threads, lds)) cands.push_back(pl);
             }
     }
+    if (gram_form(pb->B, pb->U, pb->S)) {   // one launch whatever the plan: nothing to choose
+        Params P;
+        int npl, threads;
+        size_t lds;
+        ocd_plan pl;
+        if (choose_train_params(pb, lambda, P, npl, threads, lds, &pl)) cands.assign(1, pl);
+    }
     if (cands.empty()) return OCD_EUNSUPPORTED;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return OCD_EDEVICE;
@@ -1078,6 +1085,8 @@ extern "C" ocd_status ocd_autotune_backward(const ocd_problem *pb, const void *H
                 if (make_params(pb, pl, lambda, true, P, npl, threads, lds)) cands.push_back(pl);
             }
     }
+    if (gram_form(pb->B, pb->U, pb->S))   // one launch whatever the plan: nothing to choose
+        cands.assign(1, heuristic_plan(pb, lambda, true, false));
     if (cands.empty()) return OCD_EUNSUPPORTED;
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return OCD_EDEVICE;
