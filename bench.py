@@ -59,17 +59,18 @@ def algorithmic(B, U, S, K, Q, cbytes=8):
     return flops, nbytes
 
 
-def gram_form(B, U, S):
+def gram_form(B, U, S, K):
     """The shapes that the library detects in the Gram form (U-long updates through
     H^H H) rather than with two B-long passes per update."""
-    return B >= 2 * U and (U > 8 or S >= 3 or B > 256)
+    work = U * K >= 16 if U <= 8 else U * K >= 20 if U <= 16 else B * U * K >= 4096
+    return work and B >= 2 * U and (U > 8 or S >= 3 or B > 256)
 
 
 def executed_flops(B, U, S, K):
     """Real flops per vector of the form the library runs, 8 per complex MAC: the Gram
     matrix's upper triangle shared by S symbols, the matched filters U B and K U updates
     of U entries; else the two B-long passes per update of algorithmic()."""
-    if not gram_form(B, U, S):
+    if not gram_form(B, U, S, K):
         return algorithmic(B, U, S, K, 2)[0]
     return 4.0 * U * (U + 1) * B / S + 8.0 * U * B + 8.0 * K * U * U
 
@@ -601,7 +602,7 @@ def main():
     ber = float(torch.mean(((outs[0][1] > 0).to(torch.uint8) != slots[0]["bits"]).float()).item())
 
     npl = max(2, 1 << math.ceil(math.log2(max(2, math.ceil(B / plan.lanes_per_vector)))))
-    if not plan.channel_in_registers and gram_form(B, U, S):
+    if not plan.channel_in_registers and gram_form(B, U, S, K):
         fwd_kernel = "ocd::k_gram<8, SY_16, false, false, true, 4, 4>"
     elif plan.channel_in_registers:
         fwd_kernel = "ocd::k_forward_reg<%d, %d, 8, false, false>" % (plan.lanes_per_vector, npl)

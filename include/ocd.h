@@ -241,7 +241,8 @@ ocd_status ocd_detect_backward_bce_noalloc(const ocd_problem *pb, const void *H,
  *                         (0: every workgroup loads at once).
  * A detection whose channels several symbols share, or with more than 8 users, carries
  * the inner products h_u^H r through the Gram matrix instead of the residual (the same
- * iterates; B >= 2 U, and S >= 3 or U > 8 or B > 256) and runs one workgroup per
+ * iterates; B >= 2 U, S >= 3 or U > 8 or B > 256, and U K >= 16 up to 8 users, U K >=
+ * 20 up to 16, B U K >= 4096 above) and runs one workgroup per
  * subcarrier: of a plan without channel_in_registers it then takes stagger only. */
 typedef struct {
     int lanes_per_vector;

@@ -20,10 +20,15 @@
 
 namespace ocd {
 
-// Subcarriers from which one wave takes each (see gram_waves): one workgroup a compute unit.
-// Training step, one / four waves, us: 4 symbols of 128 x 16 38 / 28 at 512, 41 / 38 at 1024,
-// 49 / 56 at 1536; 14 of 128 x 8 31 / 26, 34 / 36, 41 / 54; 14 of 100 x 12 49 / 34, 52 / 62.
-constexpr int GRAD_ONE_WAVE = 1024;
+// Whether one wave takes a subcarrier (see gram_waves): from one workgroup a compute unit on,
+// or, where registers hold the four-wave form to two of its workgroups (more than 8 users
+// and 8 symbols), once those do not take all subcarriers at once.  Training step, one / four
+// waves, us: 4 symbols of 128 x 16 38 / 28 at 512, 41 / 38 at 1024, 49 / 56 at 1536; 14 of
+// 128 x 8 31 / 26, 34 / 36, 41 / 54; 14 of 100 x 12 49 / 34 at 512, 52 / 62 at 1024.
+inline bool grad_one_wave(const Params &p)
+{
+    return p.W >= (p.U > 8 && p.S > 8 ? 513 : 1024);
+}
 
 // Dynamic LDS of a launch: the contraction, the users' constants, A, the partial sums and
 // (training step) z after every sweep, for SG subcarriers of up to tsyms symbols.
@@ -466,7 +471,7 @@ static hipError_t launch_grad_w(const Params &p, int max_blocks, size_t limit, h
 {
     if constexpr (UP <= 16) {
         const int t = grad_tile_symbols<UP, SY, TRAIN, 1>(p, limit);
-        if (p.W >= GRAD_ONE_WAVE && t >= (p.S < 16 ? p.S : 16))
+        if (grad_one_wave(p) && t >= (p.S < 16 ? p.S : 16))
             return launch_grad_k<UP, SY, F16, BOX, TRAIN, 1>(p, max_blocks, limit, s);
     }
     return launch_grad_k<UP, SY, F16, BOX, TRAIN, 4>(p, max_blocks, limit, s);

@@ -28,13 +28,13 @@ def ocd():
 
 CASES = [
     # B, U, W, S, Q, K, mode, storage: a tile's last user, symbol or antenna, and the next
-    (16, 8, 5, 3, 4, 3, "mmse", "f32"), (18, 9, 4, 8, 6, 2, "box", "f32"),
-    (32, 16, 3, 9, 2, 4, "mmse", "f16"), (34, 17, 3, 16, 4, 3, "box", "f32"),
+    (16, 8, 5, 3, 4, 3, "mmse", "f32"), (18, 9, 4, 8, 6, 3, "box", "f32"),
+    (32, 16, 3, 9, 2, 4, "mmse", "f16"), (34, 17, 3, 16, 4, 8, "box", "f32"),
     (64, 32, 2, 17, 6, 2, "mmse", "f32"), (62, 31, 2, 8, 4, 3, "hybrid", "f16"),
-    (2, 1, 7, 3, 2, 1, "box", "f32"), (63, 4, 5, 14, 6, 3, "mmse", "f32"),
+    (2, 1, 7, 3, 2, 16, "box", "f32"), (63, 4, 5, 14, 6, 4, "mmse", "f32"),
     (65, 12, 3, 33, 4, 2, "box", "f16"), (127, 8, 4, 14, 6, 3, "mmse", "f32"),
     (128, 8, 4, 14, 6, 3, "hybrid", "f16"), (130, 20, 3, 5, 4, 3, "box", "f32"),
-    (136, 32, 2, 15, 2, 4, "hybrid", "f32"), (264, 3, 4, 1, 4, 3, "mmse", "f32"),
+    (136, 32, 2, 15, 2, 4, "hybrid", "f32"), (264, 3, 4, 1, 4, 6, "mmse", "f32"),
     (100, 12, 6, 1, 4, 3, "box", "f32"), (96, 24, 4, 2, 6, 3, "hybrid", "f32"),
     (1024, 8, 2, 4, 4, 2, "mmse", "f16"), (7, 3, 300, 6, 4, 256, "mmse", "f32"),
 ]
@@ -103,8 +103,8 @@ def test_one_vector_does_not_touch_another(ocd):
 MANY = [
     # B, U, W, S, Q, K, mode, storage: one wave per subcarrier, around its
     # groups of four subcarriers, the users of a tile (8, 16) and its symbols (4, 8, 16)
-    (32, 16, 2049, 3, 4, 3, "box", "f32"), (64, 9, 2051, 5, 4, 2, "mmse", "f16"),
-    (17, 8, 2050, 8, 2, 2, "hybrid", "f32"), (40, 3, 1025, 17, 4, 3, "box", "f32"),
+    (32, 16, 2049, 3, 4, 3, "box", "f32"), (64, 9, 2051, 5, 4, 3, "mmse", "f16"),
+    (17, 8, 2050, 8, 2, 2, "hybrid", "f32"), (40, 3, 1025, 17, 4, 6, "box", "f32"),
     (128, 16, 2048, 4, 4, 2, "hybrid", "f32"),
 ]
 
@@ -142,10 +142,10 @@ def test_many_subcarriers_equal_few(ocd, case):
 
 GRADS = [
     # B, U, W, S, Q, K, mode, storage
-    (16, 8, 5, 3, 4, 3, "box", "f32"), (34, 9, 6, 8, 2, 2, "mmse", "f32"),
-    (64, 16, 5, 9, 4, 3, "hybrid", "f16"), (35, 17, 3, 16, 4, 2, "hybrid", "f32"),
-    (66, 32, 2, 17, 6, 3, "box", "f32"), (63, 5, 1025, 3, 4, 2, "hybrid", "f32"),
-    (32, 12, 1027, 4, 4, 2, "box", "f32"), (272, 4, 3, 1, 4, 3, "mmse", "f16"),
+    (16, 8, 5, 3, 4, 3, "box", "f32"), (34, 9, 6, 8, 2, 3, "mmse", "f32"),
+    (64, 16, 5, 9, 4, 3, "hybrid", "f16"), (35, 17, 3, 16, 4, 7, "hybrid", "f32"),
+    (66, 32, 2, 17, 6, 3, "box", "f32"), (63, 5, 1025, 3, 4, 4, "hybrid", "f32"),
+    (32, 12, 1027, 4, 4, 2, "box", "f32"), (272, 4, 3, 1, 4, 4, "mmse", "f16"),
     (64, 32, 3, 2, 4, 256, "mmse", "f32"),
 ]
 
