@@ -674,8 +674,9 @@ __device__ __forceinline__ void gram_run(const Params &P, long w, int i, const d
         double2 t[R], lo[BOX ? R : 1], hi[BOX ? R : 1];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const double dl = -d[r] * lam;
-            t[r] = make_double2(dl * z[r].x, dl * z[r].y);
+            // p_u - 1: -d lambda, or -1 with d = 0, where z_u goes to p_u z_u = 0
+            const double e = d[r] > 0.0 ? -d[r] * lam : -1.0;
+            t[r] = make_double2(e * z[r].x, e * z[r].y);
             if constexpr (BOX) {
                 lo[r] = make_double2(-beta - z[r].x, -beta - z[r].y);
                 hi[r] = make_double2(beta - z[r].x, beta - z[r].y);

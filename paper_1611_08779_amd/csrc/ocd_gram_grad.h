@@ -240,7 +240,9 @@ __device__ __forceinline__ void grad_reverse(const Params &P, long w0, int s0, i
         // a user's update of this sweep: a = d (z_bar - w), 0 in a clipped component (whose
         // t = z_bar - w goes to beta_bar); z_bar then is w + p c_bar = z_bar - lambda a
         // (p = 1 - lambda d), or w = z_bar - t where clipped.  z_bar changes once per sweep,
-        // so all but the FMA in w_u are formed before it and after it.
+        // so all but the FMA in w_u are formed before it and after it.  With d = 0 it is w
+        // too: no user's a changes w_u then, as g_u + lambda is 0 with h_u = 0 or infinite
+        // with lambda, for every user.
         float2 zn[R];
         double2 dm[R], sv[R], asum[R], tsum[BOX ? R : 1];
 #pragma unroll
@@ -293,6 +295,7 @@ __device__ __forceinline__ void grad_reverse(const Params &P, long w0, int s0, i
             }
             zb[r].x -= step.x;
             zb[r].y -= step.y;
+            if (!(d[r] > 0.0)) zb[r] = wv[r];
         }
         add_part(part, k, x.active ? (float)lam_bar : 0.f);
     }

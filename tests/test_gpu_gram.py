@@ -189,3 +189,38 @@ def test_gram_gradients_edges(ocd, case):
             assert abs(float(host(b)[0]) - dbeta_o) <= GRAD_TOL * abs(dbeta_o)
     want = np.mean(np.logaddexp(0.0, np.where(wl["bits"] != 0, -Lh, Lh)))
     assert abs(float(host(loss)[0]) - want) <= 1e-5 * want
+
+
+@pytest.mark.parametrize("B,U,W,S,mode", [(64, 8, 5, 3, "mmse"), (40, 12, 4, 4, "hybrid"),
+                                          (64, 16, 3, 9, "mmse"), (64, 20, 3, 4, "hybrid"),
+                                          (32, 8, 1026, 3, "hybrid")])
+def test_sweep_with_infinite_regulariser(ocd, B, U, W, S, mode):
+    """d^-1 = p = 0: an infinite lambda_k sends every z_u to 0 in sweep k and cuts the
+    gradient there; a zero column with lambda_k = 0 stays at 0.  Detection and both
+    gradients against the oracle."""
+    say("infinite lambda", B, U, W, S, mode)
+    Q, K = 4, 4
+    wl = synth.make_workload(B, U, W, S, Q, 10.0, seed=[214, B, U, S])
+    N0 = float(np.float32(wl["N0"]))
+    lam = np.array([N0, np.inf, 0.0, N0], np.float32)
+    H, beta = wl["H"].copy(), 0.0 if mode == "mmse" else float(np.float32(0.8))
+    H[1, U - 1] = 0
+    Ht, yt, lt = dev(H), dev(wl["y"]), dev(lam)
+    bits = torch.from_numpy(wl["bits"]).cuda()
+    z, L, zh = ocd.detect(Ht, yt, K, Q, mode, N0, 1.0, beta, lam=lt, want_hist=True)
+    dlam, _, dy = ocd.backward(Ht, yt, zh, None, K, Q, mode, N0, 1.0, beta, bits=bits, lam=lt)
+    _, dlam2, _, dy2, z2, L2 = ocd.train_step(Ht, yt, bits, K, Q, mode, N0, 1.0, beta, lam=lt,
+                                              want_z=True, want_llr=True)
+    torch.cuda.synchronize()
+    zo, Lo, zho = oracle_ref(H, wl["y"], K, Q, mode, N0, 1.0, lam, beta, True)
+    assert not host(zh)[:, :, 1].any()
+    for k in range(K):
+        assert z_rel_err(host(zh)[:, :, k], zho[:, :, k]) <= Z_TOL_F32
+    assert llr_rel_err(host(L), Lo) <= LLR_TOL_F32
+    assert torch.equal(z, z2) and torch.equal(L, L2) and torch.equal(dy, dy2)
+    Lh = host(L).astype(np.float64)
+    dllr = (1.0 / (1.0 + np.exp(-Lh)) - wl["bits"]) / Lh.size
+    dlam_o, _, dy_o = oracle.grad(H, wl["y"], dllr, K, Q, mode, N0=N0, lam=lam, beta=beta)
+    for a, b in ((dlam, dlam_o), (dlam2, dlam_o), (dy, dy_o)):
+        a, b = host(a).ravel(), np.asarray(b).ravel()
+        assert np.linalg.norm(a - b) <= GRAD_TOL * np.linalg.norm(b)
