@@ -650,6 +650,19 @@ __device__ __forceinline__ double gram_coefs(const Params &P, long w, int k, int
     return lam;
 }
 
+// p_u - 1 in sweep k: -d lambda, or -1 with d = 0, where z_u goes to p_u z_u = 0; with
+// given d^-1 and p that are not those of g and lambda, by p itself.
+__device__ __forceinline__ double gram_pull(const Params &P, long w, int k, int u, float g,
+                                            double d, double lam)
+{
+    if (P.p_in) {
+        float p;
+        const float di = gram_dinv(P, w, k, u, g, (float)lam, &p), den = g + (float)lam;
+        if (!(den > 0.f && di == 1.0f / den && p == di * g)) return (double)p - 1.0;
+    }
+    return d > 0.0 ? -d * lam : -1.0;
+}
+
 // The K sweeps of one vector on L lanes, lane i owning users i R .. i R + R - 1 (R =
 // UP / L): G the Gram matrix, q this lane's matched filters; sweep_done(k) with z in the
 // lane's z after every sweep.  z_u changes once per sweep, at its own update, so what
@@ -674,8 +687,8 @@ __device__ __forceinline__ void gram_run(const Params &P, long w, int i, const d
         double2 t[R], lo[BOX ? R : 1], hi[BOX ? R : 1];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            // p_u - 1: -d lambda, or -1 with d = 0, where z_u goes to p_u z_u = 0
-            const double e = d[r] > 0.0 ? -d[r] * lam : -1.0;
+            const int u = min(i * R + r, U - 1);
+            const double e = gram_pull(P, w, k, u, us[u].g, d[r], lam);
             t[r] = make_double2(e * z[r].x, e * z[r].y);
             if constexpr (BOX) {
                 lo[r] = make_double2(-beta - z[r].x, -beta - z[r].y);

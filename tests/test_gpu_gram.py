@@ -224,3 +224,40 @@ def test_sweep_with_infinite_regulariser(ocd, B, U, W, S, mode):
     for a, b in ((dlam, dlam_o), (dlam2, dlam_o), (dy, dy_o)):
         a, b = host(a).ravel(), np.asarray(b).ravel()
         assert np.linalg.norm(a - b) <= GRAD_TOL * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("B,U,W,S,per_sweep,box", [(64, 8, 5, 3, False, False), (40, 12, 4, 4, True, True),
+                                                   (64, 20, 3, 4, True, False),
+                                                   (32, 16, 2049, 3, False, True)])
+def test_given_preprocessing_is_what_the_updates_take(ocd, B, U, W, S, per_sweep, box):
+    """Updates take the given d^-1 and p also where they are not those of g and lambda:
+    z = proj(d^-1 h^H r + p z) in FP64 with those very values (damped updates of some
+    users, one never updated, one held by p = 1)."""
+    say("given preprocessing", B, U, W, S, per_sweep, box)
+    Q, K = 4, 4
+    wl = synth.make_workload(B, U, W, S, Q, 15.0, seed=[215, B, U, S])
+    N0, beta = float(np.float32(wl["N0"])), float(np.float32(0.8))
+    mode = "hybrid" if box else "mmse"
+    lam = dev((N0 * np.linspace(0.5, 2.0, K)).astype(np.float32)) if per_sweep else None
+    H, y = dev(wl["H"]), dev(wl["y"])
+    g, dinv, p = ocd.preprocess(H, K, Q, mode, N0, lam=lam)
+    dinv[..., ::3] *= 0.75
+    p[..., ::3] = 1.0 - 0.75 * (1.0 - p[..., ::3])
+    dinv[..., 1] = 0.0
+    p[..., 1] = 0.0
+    p[..., U - 1] = 1.0
+    z, _, _ = ocd.detect(H, y, K, Q, mode, N0, 1.0, beta, lam=lam, pre=(g, dinv, p))
+    torch.cuda.synchronize()
+    Hd, r = wl["H"].astype(np.complex128), wl["y"].astype(np.complex128)
+    d64 = np.broadcast_to(host(dinv).astype(np.float64).reshape(W, -1, U), (W, K, U))
+    p64 = np.broadcast_to(host(p).astype(np.float64).reshape(W, -1, U), (W, K, U))
+    zr = np.zeros((W, S, U), np.complex128)
+    for k in range(K):
+        for u in range(U):
+            h = Hd[:, None, u]
+            c = (d64[:, k, u, None] * np.sum(h.conj() * r, -1) + p64[:, k, u, None] * zr[..., u])
+            if box:
+                c = np.clip(c.real, -beta, beta) + 1j * np.clip(c.imag, -beta, beta)
+            r = r - h * (c - zr[..., u])[..., None]
+            zr[..., u] = c
+    assert z_rel_err(host(z), zr) <= Z_TOL_F32
