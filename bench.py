@@ -603,7 +603,7 @@ def main():
 
     npl = max(2, 1 << math.ceil(math.log2(max(2, math.ceil(B / plan.lanes_per_vector)))))
     if not plan.channel_in_registers and gram_form(B, U, S, K):
-        fwd_kernel = "ocd::k_gram<8, SY_16, false, false, true, 4, 4>"
+        fwd_kernel = "ocd::k_gram<8, SY_16, false, false, true, false, 4>"
     elif plan.channel_in_registers:
         fwd_kernel = "ocd::k_forward_reg<%d, %d, 8, false, false>" % (plan.lanes_per_vector, npl)
     else:

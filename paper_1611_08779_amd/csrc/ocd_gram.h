@@ -13,18 +13,22 @@
 //
 // A workgroup is four waves on one subcarrier (and up to 16 symbols of it) or, where there
 // are many (gram_waves), a wave on each of four subcarriers.
-//   1. The contraction, on the FP32 matrix cores (v_mfma_f32_16x16x4f32).  A row of H or
-//      y is 2B floats; Re h^H x is the dot product of two such rows and Im h^H x that of
-//      x with the row of j h (-Im, Re pairs).  A lane of the matrix operand holds row
-//      l mod 16, and since both operands may permute the summation index alike, its four
-//      K steps take the four floats of one 16-byte load: the operands go from HBM to
-//      registers in the matrix layout, with no staging.  Four waves split the antennas into
-//      four segments; one wave takes them in turn with the same sums, so both give the
-//      same bits.
-//   2. The matrix cores sum only CH x 4 products in FP32; those sums are added in FP64.
-//      A whole sum of 2B products in FP32 leaves an error of 1.5e-7 in z, twice the
-//      residual form's (whose rounding averages over the B entries of r); with FP64
-//      sums of 8 products and FP64 updates it is below it (0.5-0.9 times, B >= 2 U).
+//   1. The contraction, on the matrix cores.  A row of H or y is 2B floats; Re h^H x is the
+//      dot product of two such rows and Im h^H x that of x with the row of j h (-Im, Re
+//      pairs).  A lane of the matrix operand holds row l mod 16, and since both operands
+//      may permute the summation index alike, its four K steps take the four floats of one
+//      16-byte load: the operands go from HBM to registers in the matrix layout, with no
+//      staging.  Four waves split the antennas into four segments; one wave takes them in
+//      turn with the same sums, so both give the same bits.
+//   2. The products and sums are FP64 (v_mfma_f64_16x16x4f64).  The residual form's inner
+//      products err with the residual, which shrinks from sweep to sweep; these err once,
+//      with ||h|| ||y||, and ill-conditioned channels amplify that.  With FP32 sums of 16, 8
+//      or 4 products z errs up to 5.4, 3.1 or 2.1 times as much as in the residual form
+//      (users correlated 0.99, 64 x 32), in FP64 0.13 to 0.64 times over 21 shapes and 16
+//      kinds of channels (i.i.d., users or antennas correlated 0.5 to 0.999, powers over 20
+//      to 60 dB, line of sight), and FP64 costs less than sums of 4: 248 us against 281 for
+//      3300 x 14 vectors of 256 x 32, 15.0 against 14.8 for 1200 x 14 of 128 x 8 (sums of 8:
+//      226, 13.4).  FP16 storage: see gram_half.
 //   3. The four waves' partials meet in LDS; 4 or 16 lanes then own one vector and run its
 //      updates in FP64 (full rate on this GPU).  The chain of an update is an FMA, the
 //      clip, a DPP broadcast of Delta from its owner and two FMAs; what else it takes is
@@ -44,6 +48,7 @@
 namespace ocd {
 
 typedef float f32x4_acc __attribute__((ext_vector_type(4)));
+typedef double f64x4_acc __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int GRAM_WAVES = 4;
@@ -71,9 +76,15 @@ struct GramShape {
     static constexpr int PARTS = UP == 32 ? 2 : 4;       // wave partials kept in LDS
 };
 
-// Sum over the 16 x 16 tile positions this lane holds, in FP64.
+// Sum over the 16 x 16 tile positions this lane holds, in FP64: column lane mod 16, rows
+// first, first + STEP, ..
 struct GramAcc {
-    double v[4];
+    f64x4_acc v;
+};
+template <bool HALF>
+struct GramRows {
+    static constexpr int STEP = HALF ? 1 : 4;
+    __device__ static __forceinline__ int first(int lane) { return (lane >> 4) * (HALF ? 4 : 1); }
 };
 
 // Two complex entries of a row as they are stored, loaded without a branch or a use:
@@ -214,23 +225,23 @@ __device__ __forceinline__ float comp(const float4 &q, int c)
     return c == 0 ? q.x : c == 1 ? q.y : c == 2 ? q.z : q.w;
 }
 
-// The products of one block into every tile: four K steps, FP32 sums of 4 CH products,
-// or, for FP16 storage (CH = 4), one K step of v_mfma_f32_16x16x16_f16, whose 16 products
-// are exact in FP32 and whose sums err less than a chain of FP32 steps (3.6e-8 of the sum
-// for 16 products against 6.5e-8; the chain of 4, used where the others err too much, 3.3e-8),
-// at an eighth of the matrix time.  NORM: the lane's squares of its channel rows as well (see GramNorm).
-template <int UP, GramSymbols SY, bool F16, int CH, bool NORM>
+// The products of one block into every tile: four K steps in FP64 or (HALF, FP16 storage)
+// two FP32 sums of eight products (v_mfma_f32_16x16x16_f16, the first and the second entry of
+// every pair), added in FP64.  NORM: the lane's squares of its channel rows as well (see
+// GramNorm).
+template <int UP, GramSymbols SY, bool F16, bool HALF, bool NORM>
 __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, SY>::HR, F16> &raw,
                                            int blk, int B, GramAcc (&acc)[GramShape<UP, SY>::T],
                                            GramNorm<GramShape<UP, SY>::HR> &gsq)
 {
+    static_assert(F16 || !HALF, "FP16 operands from FP16 storage");
     using Sh = GramShape<UP, SY>;
     constexpr bool S8 = Sh::S8;
     const int b = blk * 8 + ((threadIdx.x >> 4) & 3) * 2;
     const bool tail = blk * 8 + 8 > B;
-    using Op = typename std::conditional<F16, u32x2_t, float4>::type;
+    using Op = typename std::conditional<HALF, u32x2_t, float4>::type;
     auto operand = [&](const GramRaw<F16> &q) -> Op {
-        if constexpr (F16) {
+        if constexpr (HALF) {
             u32x2_t v = q.v;
             if (tail) {   // the same for the whole wave
                 if (b >= B) v.x = 0;
@@ -267,50 +278,50 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, SY>::HR
         bq = S8 ? pick(low, x.y, times_mj(x.y)) : x.y;
     }
     const f32x4_acc zero = {0.f, 0.f, 0.f, 0.f};
-    static_assert(!F16 || CH == 4, "one K step a block");
 #pragma unroll
-    for (int c0 = 0; c0 < 4; c0 += CH) {
-        f32x4_acc d[Sh::T];
-#pragma unroll
-        for (int c = c0; c < c0 + (F16 ? 1 : CH); ++c) {
-            auto mm = [&](int t, const Op &p, const Op &q) {
-                if constexpr (F16)
-                    d[t] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, p),
-                                                                 __builtin_bit_cast(f16x4_t, q), zero,
-                                                                 0, 0, 0);
-                else
-                    d[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp(p, c), comp(q, c),
-                                                                c == c0 ? zero : d[t], 0, 0, 0);
-            };
-            if constexpr (UP == 8) {
-                if constexpr (!S8) mm(0, a[0], x.h[0]);
-                if constexpr (Sh::Y) mm(Sh::T - 1, a[0], bq);
-            } else if constexpr (UP == 16) {
-                mm(0, a[0], x.h[0]);
-                mm(1, a[1], x.h[0]);
-                if constexpr (Sh::Y) mm(2, a[0], bq);
-                if constexpr (Sh::Y && !S8) mm(3, a[1], bq);
+    for (int c = 0; c < (HALF ? 2 : 4); ++c) {
+        f32x4_acc d[HALF ? Sh::T : 1];
+        auto mm = [&](int t, const Op &p, const Op &q) {
+            if constexpr (HALF) {
+                auto one = [&](const u32x2_t &x) {   // of both operands: 0 times inf is not 0
+                    return __builtin_bit_cast(f16x4_t, c == 0 ? u32x2_t{x.x, 0u} : u32x2_t{x.y, 0u});
+                };
+                d[t] = __builtin_amdgcn_mfma_f32_16x16x16f16(one(p), one(q), zero, 0, 0, 0);
             } else {
-                mm(0, a[0], x.h[0]);
-                mm(1, a[1], x.h[0]);
-                mm(2, a[0], x.h[1]);
-                mm(3, a[1], x.h[1]);
-                mm(4, a[2], x.h[1]);
-                mm(5, a[3], x.h[1]);
-                if constexpr (Sh::Y) mm(6, a[0], bq);
-                if constexpr (S8) {
-                    mm(7, a[2], bq);
-                } else if constexpr (Sh::Y) {
-                    mm(7, a[1], bq);
-                    mm(8, a[2], bq);
-                    mm(9, a[3], bq);
-                }
+                acc[t].v = __builtin_amdgcn_mfma_f64_16x16x4f64((double)comp(p, c),
+                                                                (double)comp(q, c), acc[t].v, 0, 0, 0);
+            }
+        };
+        if constexpr (UP == 8) {
+            if constexpr (!S8) mm(0, a[0], x.h[0]);
+            if constexpr (Sh::Y) mm(Sh::T - 1, a[0], bq);
+        } else if constexpr (UP == 16) {
+            mm(0, a[0], x.h[0]);
+            mm(1, a[1], x.h[0]);
+            if constexpr (Sh::Y) mm(2, a[0], bq);
+            if constexpr (Sh::Y && !S8) mm(3, a[1], bq);
+        } else {
+            mm(0, a[0], x.h[0]);
+            mm(1, a[1], x.h[0]);
+            mm(2, a[0], x.h[1]);
+            mm(3, a[1], x.h[1]);
+            mm(4, a[2], x.h[1]);
+            mm(5, a[3], x.h[1]);
+            if constexpr (Sh::Y) mm(6, a[0], bq);
+            if constexpr (S8) {
+                mm(7, a[2], bq);
+            } else if constexpr (Sh::Y) {
+                mm(7, a[1], bq);
+                mm(8, a[2], bq);
+                mm(9, a[3], bq);
             }
         }
+        if constexpr (HALF) {
 #pragma unroll
-        for (int t = 0; t < Sh::T; ++t)
+            for (int t = 0; t < Sh::T; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[t].v[r] += (double)d[t][r];
+                for (int r = 0; r < 4; ++r) acc[t].v[r] += (double)d[t][r];
+        }
     }
 }
 
@@ -318,7 +329,7 @@ __device__ __forceinline__ void gram_block(const GramBlock<GramShape<UP, SY>::HR
 // the segments then added in order: one wave per segment (NW = 4) or one wave for all of
 // them (NW = 1) give the same bits.  The next blocks' loads are in flight while the
 // current ones multiply; `between` runs when the first are out.
-template <int UP, GramSymbols SY, bool F16, bool VEC, int CH, int NW, typename Between>
+template <int UP, GramSymbols SY, bool F16, bool VEC, bool HALF, int NW, typename Between>
 __device__ __forceinline__ void gram_contract(const Params &P, const unsigned char *hb,
                                               const unsigned char *yb, int ns,
                                               GramAcc (&acc)[GramShape<UP, SY>::T],
@@ -352,7 +363,7 @@ __device__ __forceinline__ void gram_contract(const Params &P, const unsigned ch
     };
     auto multiply = [&](const GramBlock<Sh::HR, F16> &x, int e) {
         if (e >= b1) return;
-        gram_block<UP, SY, F16, CH, NW == 1>(x, e, P.B, acc, gsq);
+        gram_block<UP, SY, F16, HALF, NW == 1>(x, e, P.B, acc, gsq);
         if (NW == 1 && ((e + 1 == m1) | (e + 1 == m2) | (e + 1 == m3))) {
 #pragma unroll
             for (int t = 0; t < T; ++t)
@@ -444,7 +455,7 @@ __device__ __forceinline__ float gram_dinv(const Params &P, long w, int k, int u
 // Contraction of subcarrier w with symbols s0 .. s0 + ns - 1 by this wave (NW = 1; lds, us
 // its own) or workgroup (NW = 4), and the users' constants, ||h_u||^2 in the summation
 // order of k_preprocess, so that d^-1 and p have its bits.  Ends with a workgroup barrier.
-template <int UP, GramSymbols SY, bool F16, bool VEC, int CH, int NW>
+template <int UP, GramSymbols SY, bool F16, bool VEC, bool HALF, int NW>
 __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int ns, double *lds,
                                            GramUser *us)
 {
@@ -471,7 +482,7 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
     GramNorm<Sh::HR> gsq;
     gsq.clear();
     if constexpr (NW == 1) {
-        gram_contract<UP, SY, F16, VEC, CH, NW>(P, hb, yb, ns, acc, gsq, [] {});
+        gram_contract<UP, SY, F16, VEC, HALF, NW>(P, hb, yb, ns, acc, gsq, [] {});
 #pragma unroll
         for (int r = 0; r < Sh::HR; ++r) {
             const float g = gsq.sum(r);   // of row lane mod 16
@@ -498,7 +509,7 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
             for (int i = 0; i < 8; ++i) hg[i] = entry(u0, l16 + 16 * i);
         }
         float s0g = 0.f;
-        gram_contract<UP, SY, F16, VEC, CH, NW>(P, hb, yb, ns, acc, gsq, [&] {
+        gram_contract<UP, SY, F16, VEC, HALF, NW>(P, hb, yb, ns, acc, gsq, [&] {
             if (first_g) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) s0g = square(hg[i], l16 + 16 * i, s0g);
@@ -554,14 +565,15 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
             }
         }
     };
-    const int col = lane & 15, row = (lane >> 4) * 4;
+    using Rows = GramRows<HALF>;
+    const int col = lane & 15, row = Rows::first(lane);
     if constexpr (NW == 1) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             double sum[T];
 #pragma unroll
             for (int t = 0; t < T; ++t) sum[t] = acc[t].v[r];
-            place(col, row + r, sum);
+            place(col, row + Rows::STEP * r, sum);
         }
         __syncthreads();
         return;
@@ -569,9 +581,9 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
     auto store = [&](int p) {
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            double2 *d = reinterpret_cast<double2 *>(lds + gram_at<T>(p, t, col, row));
-            d[0] = make_double2(acc[t].v[0], acc[t].v[1]);
-            d[1] = make_double2(acc[t].v[2], acc[t].v[3]);
+            double *d = lds + gram_at<T>(p, t, col, row);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) d[Rows::STEP * r] = acc[t].v[r];
         }
     };
     if constexpr (Sh::PARTS == 2) {   // waves 2 and 3 hand theirs to 0 and 1 first
@@ -582,7 +594,7 @@ __device__ __forceinline__ void gram_front(const Params &P, long w, int s0, int 
             for (int t = 0; t < T; ++t) {
                 const double *d = lds + gram_at<T>(wave, t, col, row);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[t].v[r] += d[r];
+                for (int r = 0; r < 4; ++r) acc[t].v[r] += d[Rows::STEP * r];
             }
             store(wave);
         }
@@ -816,26 +828,27 @@ __device__ __forceinline__ void gram_sweeps(const Params &P, long w0, int s0, in
     }
 }
 
-// How long the FP32 sums of the contraction are (CH of 4 products each): 16 products from 128 antennas and four per user on, 8 from 64
-// antennas on, 4 below and for rows without vector loads, the longest whose rounding stays below the residual form's.
-// Error of z at 8-20 dB (residual form; 16, 8, 4 products):
-//   B = 128, U = 8:  5.7e-8; 4.6e-8, 3.7e-8, 3.3e-8     B = 64, U = 16: 8.0e-8; 8.8e-8, 6.6e-8, 5.1e-8
-//   B = 128, U = 32: 8.4e-8; 7.2e-8, 5.2e-8, 4.0e-8     B = 32, U = 16: 1.13e-7; 1.71e-7, 1.19e-7, 9.0e-8
-// FP16 storage takes one step of 16 products a block at any size (see gram_block).
-// f(VEC, CH) as integral constants, one return type.
-template <bool F16, typename F>
+// Whether the contraction of FP16 storage takes FP16 operands (exact products, FP32 sums of
+// eight): where z then errs no more than in the residual form on any of the channels above
+// (16 antennas a user, up to 8 users and 16 sweeps: 0.6 to 0.99 times at users correlated
+// 0.99; 256 x 16, 1.11 at 16 sweeps; 64 x 16, 1.2).  4800 x 14 vectors of 128 x 8 30 us against 40 in
+// FP64, 1200 x 14 11.8 against 14.8.
+__host__ __device__ inline bool gram_half(int B, int U, int K)
+{
+    return U <= 8 && B >= 16 * U && K <= 16;
+}
+
+// f(VEC, HALF) as integral constants, one return type.  VEC: rows of even length, aligned.
+template <int UP, bool F16, typename F>
 __host__ __device__ __forceinline__ auto gram_dispatch(const Params &P, F &&f)
 {
-    using std::integral_constant;
-    if constexpr (F16) {
-        if (P.vec_ok) return f(std::true_type{}, integral_constant<int, 4>{});
-        return f(std::false_type{}, integral_constant<int, 4>{});
-    } else {
-        if (!P.vec_ok) return f(std::false_type{}, integral_constant<int, 1>{});
-        if (P.B >= 128 && P.B >= 4 * P.U) return f(std::true_type{}, integral_constant<int, 4>{});
-        if (P.B >= 64) return f(std::true_type{}, integral_constant<int, 2>{});
-        return f(std::true_type{}, integral_constant<int, 1>{});
+    using std::false_type;
+    using std::true_type;
+    if (!P.vec_ok) return f(false_type{}, false_type{});
+    if constexpr (F16 && UP == 8) {
+        if (gram_half(P.B, P.U, P.K)) return f(true_type{}, true_type{});
     }
+    return f(true_type{}, false_type{});
 }
 
 // This wave's subcarrier of a workgroup whose first is w0.
@@ -847,13 +860,13 @@ __device__ __forceinline__ long gram_subcarrier(const Params &P, long w0)
 }
 
 // One tile: symbols s0 .. s0 + ns - 1 of the workgroup's subcarriers, from w0 on.
-template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, bool HALF, int NW>
 __device__ __forceinline__ void gram_tile(const Params &P, long w0, int s0, int ns, double *lds,
                                           GramUser *us)
 {
     using M = GramLds<UP, SY, NW>;
     const int sub = NW == 4 ? 0 : threadIdx.x >> 6;
-    gram_front<UP, SY, F16, VEC, CH, NW>(P, gram_subcarrier<NW>(P, w0), s0, ns,
+    gram_front<UP, SY, F16, VEC, HALF, NW>(P, gram_subcarrier<NW>(P, w0), s0, ns,
                                          lds + sub * M::SUMS, us + sub * UP);
     gram_sweeps<UP, SY, BOX, NW>(P, w0, s0, ns, lds, us);
 }

@@ -4,8 +4,8 @@
 
 namespace ocd {
 
-// VEC: rows of even length, aligned.  CH: see gram_dispatch.  NW: see gram_waves.
-template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
+// VEC: rows of even length, aligned.  HALF: see gram_dispatch.  NW: see gram_waves.
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, bool HALF, int NW>
 __global__ __launch_bounds__(GRAM_THREADS, UP == 32 ? 3 : 2) void k_gram(Params P, int tiles)
 {
     using M = GramLds<UP, SY, NW>;
@@ -15,13 +15,13 @@ __global__ __launch_bounds__(GRAM_THREADS, UP == 32 ? 3 : 2) void k_gram(Params 
     const int g = tiles == 1 ? (int)blockIdx.x : (int)blockIdx.x / tiles;
     const int s0 = tiles == 1 ? 0 : 16 * ((int)blockIdx.x - g * tiles);
     const int ns = min(16, P.S - s0);
-    gram_tile<UP, SY, F16, BOX, VEC, CH, NW>(P, (long)g * M::SG, s0, ns, lds, us);
+    gram_tile<UP, SY, F16, BOX, VEC, HALF, NW>(P, (long)g * M::SG, s0, ns, lds, us);
 }
 
-template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH, int NW>
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, bool HALF, int NW>
 static hipError_t launch_gram_k(const Params &p, hipStream_t s)
 {
-    auto fn = k_gram<UP, SY, F16, BOX, VEC, CH, NW>;
+    auto fn = k_gram<UP, SY, F16, BOX, VEC, HALF, NW>;
     constexpr int SG = GramLds<UP, SY, NW>::SG;
     Params q = p;
     const int tiles = (p.S + 15) / 16;
@@ -37,21 +37,21 @@ static hipError_t launch_gram_k(const Params &p, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, int CH>
+template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, bool HALF>
 static hipError_t launch_gram_w(const Params &p, hipStream_t s)
 {
     if constexpr (UP <= 16) {
         if (gram_waves(p.B, p.U, (long)p.W * ((p.S + 15) / 16)) == 1)
-            return launch_gram_k<UP, SY, F16, BOX, VEC, CH, 1>(p, s);
+            return launch_gram_k<UP, SY, F16, BOX, VEC, HALF, 1>(p, s);
     }
-    return launch_gram_k<UP, SY, F16, BOX, VEC, CH, 4>(p, s);
+    return launch_gram_k<UP, SY, F16, BOX, VEC, HALF, 4>(p, s);
 }
 
 template <int UP, GramSymbols SY, bool F16, bool BOX>
 static hipError_t launch_gram_c(const Params &p, hipStream_t s)
 {
-    return gram_dispatch<F16>(p, [&](auto vec, auto ch) {
-        return launch_gram_w<UP, SY, F16, BOX, vec(), ch()>(p, s);
+    return gram_dispatch<UP, F16>(p, [&](auto vec, auto half) {
+        return launch_gram_w<UP, SY, F16, BOX, vec(), half()>(p, s);
     });
 }
 

@@ -370,8 +370,8 @@ __device__ __forceinline__ void grad_front(const Params &P, long w0, int s0, int
     const long w = gram_subcarrier<NW>(P, w0);
     lds += sub * GramLds<UP, SY, NW>::SUMS;
     us += sub * UP;
-    gram_dispatch<F16>(P, [&](auto vec, auto ch) {
-        gram_front<UP, SY, F16, vec(), ch(), NW>(P, w, s0, ns, lds, us);
+    gram_dispatch<UP, F16>(P, [&](auto vec, auto half) {
+        gram_front<UP, SY, F16, vec(), half(), NW>(P, w, s0, ns, lds, us);
     });
 }
 

@@ -12,8 +12,8 @@ __device__ __forceinline__ void job_gram_tile(const Params &P, long w, int s0, i
                                               GramUser *us)
 {
     constexpr int NW = UP == 32 ? 4 : 1;
-    gram_dispatch<F16>(P, [&](auto vec, auto ch) {
-        gram_tile<UP, SY, F16, BOX, vec(), ch(), NW>(P, w, s0, ns, lds, us);
+    gram_dispatch<UP, F16>(P, [&](auto vec, auto half) {
+        gram_tile<UP, SY, F16, BOX, vec(), half(), NW>(P, w, s0, ns, lds, us);
     });
 }
 

@@ -261,3 +261,58 @@ def test_given_preprocessing_is_what_the_updates_take(ocd, B, U, W, S, per_sweep
             r = r - h * (c - zr[..., u])[..., None]
             zr[..., u] = c
     assert z_rel_err(host(z), zr) <= Z_TOL_F32
+
+
+def _correlated(kind, W, U, B, rng):
+    """Channels that are not i.i.d.: users or antennas correlated, or unequal powers."""
+    H = (rng.standard_normal((W, U, B)) + 1j * rng.standard_normal((W, U, B))) / np.sqrt(2 * B)
+    what, x = kind
+    if what == "users":
+        return np.linalg.cholesky((1 - x) * np.eye(U) + x) @ H
+    if what == "antennas":
+        return H @ np.linalg.cholesky(x ** np.abs(np.subtract.outer(np.arange(B), np.arange(B)))).T
+    return H * 10 ** (-x / 20 * rng.random((W, U, 1)))   # powers spread over x dB
+
+
+@pytest.mark.parametrize("kind", [("users", 0.9), ("users", 0.99), ("antennas", 0.99), ("powers", 30.0)])
+@pytest.mark.parametrize("B,U,K,storage", [(128, 8, 3, "f32"), (128, 8, 3, "f16"), (64, 8, 4, "f32"),
+                                           (32, 8, 4, "f32"), (40, 7, 4, "f16"), (32, 16, 4, "f32"),
+                                           (64, 32, 4, "f32"), (48, 24, 4, "f16"), (256, 32, 5, "f32"),
+                                           (51, 12, 4, "f32")])
+def test_error_on_ill_conditioned_channels(ocd, B, U, K, storage, kind):
+    """The error of z where users or antennas are correlated or powers unequal: the inner
+    products are FP64, so what is left are the roundings of g, den, d^-1 and z, 2^-24 each
+    (root mean square over the vectors at most 4 x 2^-24), and no more than the residual
+    form's, which up to 8 users a plan with the channel in registers runs."""
+    say("ill-conditioned", B, U, K, storage, kind)
+    W, S, Q = 32, 7, 4
+    rng = np.random.default_rng([216, B, U, int(100 * kind[1])])
+    H = _correlated(kind, W, U, B, rng)
+    x = (rng.choice([-3, -1, 1, 3], (W, S, U)) + 1j * rng.choice([-3, -1, 1, 3], (W, S, U))) / np.sqrt(10)
+    N0 = float(np.float32(0.01))
+    y = x @ H + np.sqrt(N0 / 2) * (rng.standard_normal((W, S, B)) + 1j * rng.standard_normal((W, S, B)))
+    if storage == "f16":
+        Hx, yx = to_f16_pairs(H), to_f16_pairs(y)
+        Hr, yr = from_f16_pairs(Hx), from_f16_pairs(yx)
+    else:
+        Hx, yx = Hr, yr = H.astype(np.complex64), y.astype(np.complex64)
+    zo, _, _ = oracle_ref(Hr, yr, K, Q, "mmse", N0)
+    Ht, yt = dev(Hx), dev(yx)
+
+    def rms():
+        z, _, _ = ocd.detect(Ht, yt, K, Q, "mmse", N0, storage=storage)
+        torch.cuda.synchronize()
+        e = np.linalg.norm(host(z) - zo, axis=-1) / np.linalg.norm(zo, axis=-1)
+        return float(np.sqrt(np.mean(e ** 2)))
+
+    e = rms()
+    say("  rms error %.3g" % e)
+    assert e <= 4 * 2.0 ** -24
+    if U <= 8:
+        pb = ocd.problem(B, U, W, S, Q, K, "mmse", storage, N0)
+        plan = ocd.ocd_get_plan(pb)
+        ocd.ocd_set_plan(pb, ocd.Plan(16, 8, 0, 1, 0))
+        r = rms()
+        ocd.ocd_set_plan(pb, plan)
+        say("  residual form %.3g" % r)
+        assert e <= r
