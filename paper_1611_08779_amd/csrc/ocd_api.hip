@@ -187,7 +187,7 @@ bool make_params(const ocd_problem *pb, const ocd_plan &pl, const float *lambda,
         return true;
     }
     lds = lds_bytes(P, threads / L, backward, threads / 64);
-    return lds <= (size_t)lds_limit_bytes();
+    return lds + (backward ? GRADIENT_STATIC_LDS : 0) <= (size_t)lds_limit_bytes();
 }
 
 // Rough occupancy model used by the heuristic: lanes doing useful work per CU.
@@ -788,7 +788,7 @@ static bool train_params(const ocd_problem *pb, const ocd_plan &pl, const float 
 {
     if (!make_params(pb, pl, lambda, true, P, npl, threads, lds)) return false;
     lds = lds_bytes(P, threads / pl.lanes_per_vector, true, threads / 64, true);
-    return lds <= (size_t)lds_limit_bytes();
+    return lds + GRADIENT_STATIC_LDS <= (size_t)lds_limit_bytes();
 }
 
 // The training step's plan: the one ocd_autotune_train cached for the shape, else

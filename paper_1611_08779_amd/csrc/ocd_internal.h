@@ -97,6 +97,10 @@ inline size_t lds_bytes(const Params &p, int vpb_cap, bool backward, int nwaves 
     return b;
 }
 
+// Static LDS of the gradient kernels (finish_partials, up to the next 16 bytes), which counts
+// towards the limit of a workgroup as well.
+constexpr size_t GRADIENT_STATIC_LDS = 272;
+
 // Bytes of dynamic LDS of an explicit-MMSE launch: staged H_w, two U x U work
 // matrices and the soft-output coefficients per slot, a matched-filter row per
 // vector and the Gram diagonal per slot.
