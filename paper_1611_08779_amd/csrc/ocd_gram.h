@@ -871,17 +871,23 @@ __device__ __forceinline__ void gram_tile(const Params &P, long w0, int s0, int 
     gram_sweeps<UP, SY, BOX, NW>(P, w0, s0, ns, lds, us);
 }
 
-// Waves per subcarrier: one where there are enough subcarriers to keep the GPU busy (no
-// partial sums to exchange, and the set-up once per subcarrier), four below, where the
-// length of a workgroup's chain counts.  One wave each gives every SIMD two waves from 2048
-// subcarriers on; fewer antennas shorten its chain and move the line to one.  One / four
-// waves, us, 14 symbols of 128 x 8: 10.9 / 10.4 at 1024 subcarriers, 15.0 / 13.7 at 1536,
-// 15.5 / 17.3 at 2048, 45 / 51 at 8192; 4 symbols of 128 x 16: 21.8 / 19.0, 22.3 / 22.4
-// (1536, 2048); 14 symbols of 32 x 8: 7.7 / 6.9, 8.1 / 8.5 (512, 1024).  Above 16 users the
-// tiles' FP64 sums of a whole subcarrier do not fit one wave's registers.
-__host__ __device__ inline int gram_waves(int B, int U, long subcarrier_tiles)
+// Waves per subcarrier: one where there are enough subcarriers (and tiles of 16 symbols of
+// them) to keep the GPU busy (no partial sums to exchange, and the set-up once per
+// subcarrier), four below, where the length of a workgroup's chain counts.  The line moves
+// down with the antennas, whose matrix products the four waves share, and for more than 8
+// users and symbols, whose sweeps keep one wave of the four busy for long.  Time with one wave over
+// time with four (K = 2, 4):
+//   32 x 8:   1.00 at 400, 0.94 at 520 (S <= 8); 1.12, 1.03, 0.99 at 700 (S > 8)
+//   64 x 8:   1.05-1.18 at 1030, 0.99-1.08 at 1300, 0.91-1.00 at 1600
+//   128 x 8:  1.03-1.14 at 2100, 0.84-0.94 at 3000;  128 x 16, S <= 8: 1.10, 0.89
+//   128 x 16, S > 8: 1.14 at 700, 0.94 at 850;  256 x 16: 1.15 at 1030, 0.93 at 1600
+// Above 16 users the tiles' FP64 sums of a whole subcarrier do not fit one wave's registers.
+__host__ __device__ inline int gram_waves(int B, int U, int S, long subcarrier_tiles)
 {
-    return U <= 16 && subcarrier_tiles >= (B <= 64 ? 1024 : 2048) ? 1 : 4;
+    if (U > 16) return 4;
+    const long line = U > 8 && S > 8 ? (B <= 128 ? 800 : 1500)
+                      : U <= 8 && B <= 32 ? 600 : B <= 64 ? 1280 : 2500;
+    return subcarrier_tiles >= line ? 1 : 4;
 }
 
 }  // namespace ocd

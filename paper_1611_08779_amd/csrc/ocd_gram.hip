@@ -41,7 +41,7 @@ template <int UP, GramSymbols SY, bool F16, bool BOX, bool VEC, bool HALF>
 static hipError_t launch_gram_w(const Params &p, hipStream_t s)
 {
     if constexpr (UP <= 16) {
-        if (gram_waves(p.B, p.U, (long)p.W * ((p.S + 15) / 16)) == 1)
+        if (gram_waves(p.B, p.U, p.S, (long)p.W * ((p.S + 15) / 16)) == 1)
             return launch_gram_k<UP, SY, F16, BOX, VEC, HALF, 1>(p, s);
     }
     return launch_gram_k<UP, SY, F16, BOX, VEC, HALF, 4>(p, s);

@@ -20,14 +20,20 @@
 
 namespace ocd {
 
-// Whether one wave takes a subcarrier (see gram_waves): from one workgroup a compute unit on,
-// or, where registers hold the four-wave form to two of its workgroups (more than 8 users
-// and 8 symbols), once those do not take all subcarriers at once.  Training step, one / four
-// waves, us: 4 symbols of 128 x 16 38 / 28 at 512, 41 / 38 at 1024, 49 / 56 at 1536; 14 of
-// 128 x 8 31 / 26, 34 / 36, 41 / 54; 14 of 100 x 12 49 / 34 at 512, 52 / 62 at 1024.
-inline bool grad_one_wave(const Params &p)
+// Whether one wave takes a subcarrier (see gram_waves): from two tiles a compute unit on, or
+// where four waves share long sweeps or contractions, from three or four.  Time with one wave over time with
+// four, K = 4, at 520 / 700 / 1000 subcarriers:
+//   adjoint         128 x 4, S = 8: 0.96 / 0.90 / 0.79;   64 x 8, S = 14: 1.09 / 1.00 / 0.88;
+//                   128 x 16, S = 4: 0.63 / 0.60 / 0.59;  256 x 16, S = 14: 1.06 / 1.01 / 0.94
+//   training step   32 x 8, S = 8: 0.90 / 0.84 / 0.75;    64 x 8, S = 14: 1.15 / 1.08 / 0.96;
+//                   128 x 16, S = 4: 1.29 / 1.23 / 1.08
+template <bool TRAIN>
+bool grad_one_wave(const Params &p)
 {
-    return p.W >= (p.U > 8 && p.S > 8 ? 513 : 1024);
+    const long tiles = (long)p.W * ((p.S + 15) / 16);
+    if (p.U <= 8) return tiles > (p.S <= 8 ? 512 : 768);
+    if (p.S <= 8) return tiles > (TRAIN ? 1023 : 512);
+    return tiles > (TRAIN || p.B <= 128 ? 512 : 768);
 }
 
 // Dynamic LDS of a launch: the contraction, the users' constants, A, the partial sums and
@@ -474,7 +480,7 @@ static hipError_t launch_grad_w(const Params &p, int max_blocks, size_t limit, h
 {
     if constexpr (UP <= 16) {
         const int t = grad_tile_symbols<UP, SY, TRAIN, 1>(p, limit);
-        if (grad_one_wave(p) && t >= (p.S < 16 ? p.S : 16))
+        if (grad_one_wave<TRAIN>(p) && t >= (p.S < 16 ? p.S : 16))
             return launch_grad_k<UP, SY, F16, BOX, TRAIN, 1>(p, max_blocks, limit, s);
     }
     return launch_grad_k<UP, SY, F16, BOX, TRAIN, 4>(p, max_blocks, limit, s);
