@@ -59,18 +59,27 @@ def algorithmic(B, U, S, K, Q, cbytes=8):
     return flops, nbytes
 
 
-def gram_form(B, U, S, K):
+def gram_form(B, U, W, S, K):
     """The shapes that the library detects in the Gram form (U-long updates through
-    H^H H) rather than with two B-long passes per update."""
-    work = U * K >= 16 if U <= 8 else U * K >= 20 if U <= 16 else B * U * K >= 4096
-    return work and B >= 2 * U and (U > 8 or S >= 3 or B > 256)
+    H^H H) rather than with two B-long passes per update: gram_form of csrc/ocd_forms.h."""
+    n, tiles = U * K, W * ((S + 15) // 16)
+    base = n >= 16 if U <= 8 else n >= 20 if U <= 16 else B * n >= 4096
+    if not base or B < 2 * U or (U <= 8 and S < 3 and B <= 256):
+        return False
+    if U <= 8:
+        return not (U <= 4 and S <= 4 and n < 24 and B >= 128 and tiles > 2048)
+    if S > 16:
+        return tiles <= 512 or B > 256 or (K >= 3 if U <= 16 else B * n >= 24576)
+    if U <= 16:
+        return not (U <= 10 and S <= 4 and n < 40 and tiles > 4096)
+    return not (S >= 3 and n < 32) and not (U <= 24 and K <= 2 and S > 8 and tiles > 512)
 
 
-def executed_flops(B, U, S, K):
+def executed_flops(B, U, W, S, K):
     """Real flops per vector of the form the library runs, 8 per complex MAC: the Gram
     matrix's upper triangle shared by S symbols, the matched filters U B and K U updates
     of U entries; else the two B-long passes per update of algorithmic()."""
-    if not gram_form(B, U, S, K):
+    if not gram_form(B, U, W, S, K):
         return algorithmic(B, U, S, K, 2)[0]
     return 4.0 * U * (U + 1) * B / S + 8.0 * U * B + 8.0 * K * U * U
 
@@ -576,7 +585,7 @@ def main():
     nvec = W * S
     bits_per_step = nvec * U * Q
     residual_flops_v, bytes_v = algorithmic(B, U, S, K, Q)
-    flops_v = executed_flops(B, U, S, K)
+    flops_v = executed_flops(B, U, W, S, K)
     value = bits_per_step / t_step / 1e9
     hbm_gbps = bytes_v * nvec / t_step / 1e9
     ach_tflops = flops_v * nvec / t_kernel / 1e12
@@ -602,7 +611,7 @@ def main():
     ber = float(torch.mean(((outs[0][1] > 0).to(torch.uint8) != slots[0]["bits"]).float()).item())
 
     npl = max(2, 1 << math.ceil(math.log2(max(2, math.ceil(B / plan.lanes_per_vector)))))
-    if not plan.channel_in_registers and gram_form(B, U, S, K):
+    if not plan.channel_in_registers and gram_form(B, U, W, S, K):
         fwd_kernel = "ocd::k_gram<8, SY_16, false, false, true, false, 4>"
     elif plan.channel_in_registers:
         fwd_kernel = "ocd::k_forward_reg<%d, %d, 8, false, false>" % (plan.lanes_per_vector, npl)
@@ -970,7 +979,7 @@ def fwd_bwd_form(torch, np, ocd, synth, dev):
     tfb, _ = time_graph(torch, GraphedSteps(torch, [fwd_bwd_fused] * 8), 400, 16)
     tfb2, _ = time_graph(torch, GraphedSteps(torch, [fwd_bwd] * 8), 400, 16)
     tf, _ = time_graph(torch, GraphedSteps(torch, [fwd_only] * 8), 400, 16)
-    fl = executed_flops(B5, U5, S5, K5)
+    fl = executed_flops(B5, U5, W5, S5, K5)
     return {
         "vectors_per_s": W5 * S5 / tts, "ms_per_step": tts * 1e3,
         "step": "one launch of ocd_detect_train_bce: detection, mean BCE of the LLRs, "
@@ -1052,7 +1061,7 @@ def jobs_form(torch, np, ocd, synth, dev):
     t_eager = e0.elapsed_time(e1) / reps
     agree = all(torch.allclose(z[j], zs[j], rtol=1e-5, atol=1e-6) for j in range(len(probs)))
     total_bits = sum(p.W * p.S * p.U * p.Q for p in probs)
-    total_flops = sum(executed_flops(p.B, p.U, p.S, p.K) * p.W * p.S for p in probs)
+    total_flops = sum(executed_flops(p.B, p.U, p.W, p.S, p.K) * p.W * p.S for p in probs)
     res = {
         "ms_one_launch_graph": t_batched, "ms_one_launch_eager": t_batched_eager,
         "ms_per_job_launches_graph": t_sep,

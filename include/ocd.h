@@ -240,10 +240,13 @@ ocd_status ocd_detect_backward_bce_noalloc(const ocd_problem *pb, const void *H,
  *                         first and start computing while later ones load
  *                         (0: every workgroup loads at once).
  * A detection whose channels several symbols share, or with more than 8 users, carries
- * the inner products h_u^H r through the Gram matrix instead of the residual (the same
- * iterates; B >= 2 U, S >= 3 or U > 8 or B > 256, and U K >= 16 up to 8 users, U K >=
- * 20 up to 16, B U K >= 4096 above) and runs one workgroup per
- * subcarrier: of a plan without channel_in_registers it then takes stagger only. */
+ * the inner products h_u^H r through the Gram matrix instead of the residual, where that
+ * is the faster (the same iterates; B >= 2 U, S >= 3 or U > 8 or B > 256, and U K >= 16 up to
+ * 8 users, U K >= 20 up to 16, B U K >= 4096 above; less where few users or symbols
+ * fill its tiles), and of a plan without channel_in_registers then takes stagger only.
+ * The gradients, and a detection that writes z_hist for them, do so on fewer shapes
+ * (many subcarriers, more than 8 symbols, few updates keep the residual), so z of a
+ * detection with and without z_hist agree to rounding. */
 typedef struct {
     int lanes_per_vector;
     int vectors_per_block;

@@ -386,7 +386,9 @@ ocd_status run_forward(const ocd_problem *pb, const ocd_plan &pl, const void *H,
                            z, llr, z_hist, stream);
     }
     const bool f16 = pb->storage == OCD_STORE_F16;
-    if (!pl.channel_in_registers && gram_form(pb->B, pb->U, pb->S, pb->K))
+    const bool gram = z_hist ? gram_gradient(pb->B, pb->U, pb->W, pb->S, pb->K)
+                             : gram_form(pb->B, pb->U, pb->W, pb->S, pb->K);
+    if (!pl.channel_in_registers && gram)
         return launch_gram(f16, P, stream) == hipSuccess ? OCD_OK : OCD_EDEVICE;
     hipError_t e = pl.channel_in_registers
                        ? launch_forward_reg(pl.lanes_per_vector, npl, P.reg_uc, f16, P, threads,
@@ -552,7 +554,7 @@ static ocd_status autotune_forward(const ocd_problem *pb, int n, const void *con
     }
     repeats = std::max(1, std::min(repeats, 100));
     std::vector<ocd_plan> cands;
-    const bool gram = gram_form(pb->B, pb->U, pb->S, pb->K);
+    const bool gram = gram_form(pb->B, pb->U, pb->W, pb->S, pb->K);
     if (gram)   // the Gram form has one mapping: only the staggered starts are left to tune
         cands.push_back(heuristic_plan(pb, nullptr, false, false));
     for (int L : {4, 8, 16, 32}) {
@@ -736,7 +738,7 @@ static ocd_status run_backward(const ocd_problem *pb, const ocd_plan &pl, const 
     P.dbeta = dbeta;
     set_vec_ok(P, pb, H, y);
     hipError_t e;
-    if (pb->W > 0 && gram_form(pb->B, pb->U, pb->S, pb->K)) {
+    if (pb->W > 0 && gram_gradient(pb->B, pb->U, pb->W, pb->S, pb->K)) {
         e = launch_gram_backward(pb->storage == OCD_STORE_F16, P, gram_max_blocks(P),
                                  lds_limit_bytes(), stream);
     } else if (pb->W > 0) {
@@ -863,7 +865,7 @@ static ocd_status run_train(const ocd_problem *pb, Params P, int L, int npl, int
     P.loss = loss;
     set_vec_ok(P, pb, H, y);
     hipError_t e;
-    if (pb->W > 0 && gram_form(pb->B, pb->U, pb->S, pb->K)) {
+    if (pb->W > 0 && gram_gradient(pb->B, pb->U, pb->W, pb->S, pb->K)) {
         e = launch_gram_train(pb->storage == OCD_STORE_F16, P, gram_max_blocks(P),
                               lds_limit_bytes(), stream);
     } else if (pb->W > 0) {
@@ -932,7 +934,7 @@ extern "C" ocd_status ocd_autotune_train(const ocd_problem *pb, const void *H, c
                 if (train_params(pb, pl, lambda, P, npl, threads, lds)) cands.push_back(pl);
             }
     }
-    if (gram_form(pb->B, pb->U, pb->S, pb->K)) {   // one launch whatever the plan: nothing to choose
+    if (gram_gradient(pb->B, pb->U, pb->W, pb->S, pb->K)) {   // one launch: nothing to choose
         Params P;
         int npl, threads;
         size_t lds;
@@ -1085,7 +1087,7 @@ extern "C" ocd_status ocd_autotune_backward(const ocd_problem *pb, const void *H
                 if (make_params(pb, pl, lambda, true, P, npl, threads, lds)) cands.push_back(pl);
             }
     }
-    if (gram_form(pb->B, pb->U, pb->S, pb->K))   // one launch whatever the plan: nothing to choose
+    if (gram_gradient(pb->B, pb->U, pb->W, pb->S, pb->K))   // one launch: nothing to choose
         cands.assign(1, heuristic_plan(pb, lambda, true, false));
     if (cands.empty()) return OCD_EUNSUPPORTED;
     hipEvent_t e0, e1;

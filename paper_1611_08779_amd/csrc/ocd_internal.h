@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "ocd_forms.h"
+
 namespace ocd {
 
 // Everything a forward or backward launch needs, by value.
@@ -121,22 +123,6 @@ inline bool latency_bound(const Params &p, int threads)
 {
     const int cus = device_cu_count();
     return cus > 0 && (long)p.nblocks * (threads / 64) <= 2L * 4 * cus;
-}
-
-// Whether a detection carries the inner products h_u^H r through the Gram matrix
-// (ocd_gram.h) instead of the residual.  From B = 2 U on the rounding of the products
-// stays below the residual form's.  Few users' channel fits the registers
-// (ocd_forward_reg.hip), where the residual form takes 0.24-0.9 of the Gram form's time up
-// to S = 2.  Elsewhere the contraction costs the same whatever K is, for 8, 16 or 32 users,
-// and the residual form grows with U K, from 17 users on (whose tiles of 32 x 32 hide less)
-// with B U K.  Time of the Gram form over the residual form's, residual kept left of each
-// line, FP32, S = 1 to 14: U = 4, K = 1, 2: 0.9-1.35; U = 4, K = 4 and U = 8: 0.4-0.97;
-// U = 9, K = 1, 2: 0.9-1.16; U = 9, K = 4, U = 12, K = 2: 0.5-0.95; 40 x 17, K = 1 to 4:
-// 0.9-1.54, 64 x 24, K = 1, 2: 0.9-1.19; 64 x 24, K = 4, 256 x 32: 0.4-0.95.
-inline bool gram_form(int B, int U, int S, int K)
-{
-    const bool work = U <= 8 ? U * K >= 16 : U <= 16 ? U * K >= 20 : (long)B * U * K >= 4096;
-    return work && B >= 2 * U && (U > 8 || S >= 3 || B > 256);
 }
 
 // Launchers (one per template instantiation, selected at run time).

@@ -183,7 +183,7 @@ static bool job_shape_built(int L, int npl)
 // The kernel that runs a job (see N_JOB_KERNELS).
 static int job_kernel(const Params &P)
 {
-    if (!gram_form(P.B, P.U, P.S, P.K)) return 0;
+    if (!gram_form(P.B, P.U, P.W, P.S, P.K)) return 0;
     return P.U <= 8 ? 1 : P.U <= 16 ? 2 : 3;
 }
 
@@ -547,7 +547,7 @@ extern "C" ocd_status ocd_detect_jobs(const ocd_problem *jobs, const void *const
         // tile policies and lane modes shape the residual form's tiles only
         bool residual = false;
         for (int j = 0; j < n_jobs; ++j)
-            residual |= !gram_form(jobs[j].B, jobs[j].U, jobs[j].S, jobs[j].K);
+            residual |= !gram_form(jobs[j].B, jobs[j].U, jobs[j].W, jobs[j].S, jobs[j].K);
         std::vector<std::pair<float, int>> ranked;
         for (int c = 0; c < N_CHOICES; ++c) {
             if (!residual && (choice_lane_mode(c) != 0 ||

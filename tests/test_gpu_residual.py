@@ -23,8 +23,8 @@ def ocd():
     return m
 
 
-def residual(B, U, S, K):
-    assert not bench.gram_form(B, U, S, K), "a shape of the Gram form"
+def residual(B, U, W, S, K):
+    assert not bench.gram_form(B, U, W, S, K), "a shape of the Gram form"
 
 
 @pytest.mark.parametrize("mode", ["mmse", "hybrid"])
@@ -36,7 +36,7 @@ def test_adjoint_fits_the_lds_of_every_shape(ocd, mode):
     for B in (16, 24, 32, 40, 48, 64, 80, 96, 100, 128, 200, 256):
         for U in (2, 5, 8, 12, 16, 20, 24, 31, 32):
             for S in (1, 2, 3, 4, 7, 14):
-                if U > B or bench.gram_form(B, U, S, K):
+                if U > B or bench.gram_form(B, U, W, S, K):
                     continue
                 H = torch.randn(W, U, B, dtype=torch.complex64, device="cuda")
                 y = torch.randn(W, S, B, dtype=torch.complex64, device="cuda")
@@ -53,7 +53,7 @@ def test_adjoint_fits_the_lds_of_every_shape(ocd, mode):
 
 def test_adjoint_close_to_the_lds_limit(ocd):
     B, U, W, S, Q, K = 64, 24, 5, 2, 4, 1
-    residual(B, U, S, K)
+    residual(B, U, W, S, K)
     wl = synth.make_workload(B, U, W, S, Q, 10.0, seed=[217, 0])
     N0, beta = float(np.float32(wl["N0"])), float(np.float32(0.9))
     lam = np.array([0.7 * N0], np.float32)
