@@ -67,7 +67,7 @@ def gram_form(B, U, W, S, K):
     if not base or B < 2 * U or (U <= 8 and S < 3 and B <= 256):
         return False
     if U <= 8:
-        return not (U <= 4 and S <= 4 and n < 24 and B >= 128 and tiles > 2048)
+        return not (U <= 4 and S <= 4 and n < 24 and tiles > (2048 if B >= 128 else 12000))
     if S > 16:
         return tiles <= 512 or B > 256 or (K >= 3 if U <= 16 else B * n >= 24576)
     if U <= 16:

@@ -23,7 +23,7 @@ inline bool gram_form(int B, int U, int W, int S, int K)
     const bool base = U <= 8 ? n >= 16 : U <= 16 ? n >= 20 : (long)B * n >= 4096;
     if (!base || B < 2 * U || (U <= 8 && S < 3 && B <= 256)) return false;
     const long tiles = (long)W * ((S + 15) / 16);
-    if (U <= 8) return !(U <= 4 && S <= 4 && n < 24 && B >= 128 && tiles > 2048);
+    if (U <= 8) return !(U <= 4 && S <= 4 && n < 24 && tiles > (B >= 128 ? 2048 : 12000));
     if (S > 16)
         return tiles <= 512 || B > 256 || (U <= 16 ? K >= 3 : (long)B * n >= 24576);
     if (U <= 16) return !(U <= 10 && S <= 4 && n < 40 && tiles > 4096);
@@ -43,7 +43,11 @@ inline bool gram_form(int B, int U, int W, int S, int K)
 //   U > 8, S = 17    128 x 16, K = 4: 1.54, 1.08; 256 x 16, K = 4: 1.10, 1.02; 128 x 32,
 //                    K = 2: 1.63, 1.47; K = 4: 1.01, 1.17
 //   S = 8            128 x 4, K = 4: 1.13, 1.25; 128 x 32, K = 1: 1.19, 1.25; 256 x 16, K = 2: 1.11, 1.25
-// and 1.0 or less elsewhere but for 64 x 24, K = 4, S <= 8 at 2048 (0.71, 1.24).
+// Past 2048 subcarriers, one layer of the one-wave workgroups, few antennas or a tile that the
+// users do not fill leave the residual form the faster, at 2500 to 14000 subcarriers, S = 4,
+// K = 4: 32 x 8 1.00-1.42, 1.12-1.62; 64 x 4 1.00-1.61, 1.13-1.82; 64 x 9 0.84-1.39, 1.20-1.98; 32 x 16
+// 0.76-1.29, 1.09-1.61; against 64 x 8 0.68-0.75, 0.77-1.25; 128 x 8 0.63-0.71, below 1; 64 x 16 0.63,
+// 1.11 or less.
 inline bool gram_gradient(int B, int U, int W, int S, int K)
 {
     const int n = U * K;
@@ -51,6 +55,10 @@ inline bool gram_gradient(int B, int U, int W, int S, int K)
     if (!gram_form(B, U, 1, S, K)) return false;
     if (U <= 8 && S > 16) return tiles <= 256 || (n >= 24 && work >= 2048);
     if (tiles <= 512) return true;
+    if (tiles > 2304 && U <= 16) {
+        const int full = U <= 4 ? 1024 : U <= 8 ? 512 : U <= 12 ? 1024 : 520;
+        if (B * U < full) return false;
+    }
     if (U > 8 && U <= 16 && B > 128 && K <= 2 && S > 4) return false;
     if (S <= 8) return S <= 4 || !(U <= 4 ? n < 24 : U > 16 && K == 1);
     if (U <= 8) return n >= 24;
