@@ -612,8 +612,20 @@ static hipError_t launch_fx_tile(const FxParams &p, hipStream_t s)
     const int tiles = (p.S + 15) / 16;
     const bool vec = p.B % 4 == 0 && reinterpret_cast<uintptr_t>(p.H) % 16 == 0 &&
                      reinterpret_cast<uintptr_t>(p.y) % 16 == 0;
-    hipLaunchKernelGGL(fn, dim3((unsigned)p.W * tiles), dim3(M::THREADS), lds, s, p, tiles, vec);
-    return hipGetLastError();
+    const int most = (int)groups_per_launch(tiles, M::THREADS);
+    for (long w0 = 0; w0 < p.W; w0 += most) {
+        FxParams q = p;
+        const size_t v0 = (size_t)w0 * p.S;
+        q.W = (int)(p.W - w0 < most ? p.W - w0 : most);
+        q.H = p.H + (size_t)w0 * p.U * p.B * 2;
+        q.y = p.y + v0 * p.B * 2;
+        if (p.z) q.z = p.z + v0 * p.U * 2;
+        if (p.llr) q.llr = p.llr + v0 * p.U * p.Q;
+        hipLaunchKernelGGL(fn, dim3((unsigned)q.W * tiles), dim3(M::THREADS), lds, s, q, tiles, vec);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Channels are staged when the subcarriers a workgroup can touch fit in 32 KB of

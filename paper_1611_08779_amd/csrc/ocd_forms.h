@@ -1,7 +1,14 @@
-// ocd_forms.h -- which shapes run in which form (host only, no HIP).
+// ocd_forms.h -- which shapes run in which form, and in how many launches (host only, no HIP).
 #pragma once
 
 namespace ocd {
+
+// A launch takes fewer than 2^32 work-items: the most groups of `blocks` workgroups of
+// `threads` threads that fit one (a grid with more goes out in several launches).
+inline long groups_per_launch(long blocks, int threads)
+{
+    return 0xFFFFFFFFL / threads / blocks;
+}
 
 // Whether a detection carries the inner products h_u^H r through the Gram matrix
 // (ocd_gram.h) instead of the residual.  Few users' channel fits the registers

@@ -23,8 +23,29 @@ static hipError_t launch_gram_k(const Params &p, hipStream_t s)
 {
     auto fn = k_gram<UP, SY, F16, BOX, VEC, HALF, NW>;
     constexpr int SG = GramLds<UP, SY, NW>::SG;
-    Params q = p;
     const int tiles = (p.S + 15) / 16;
+    // nearly always one launch; else whole groups of SG subcarriers each
+    const long most = groups_per_launch(tiles, GRAM_THREADS) * SG;
+    if (p.W > most) {
+        constexpr size_t c = F16 ? 4 : 8;   // bytes of an entry of H and y
+        for (long w0 = 0; w0 < p.W; w0 += most) {
+            Params q = p;
+            const long v0 = w0 * p.S, d0 = w0 * (p.per_sweep ? p.K : 1) * p.U;
+            q.W = (int)(p.W - w0 < most ? p.W - w0 : most);
+            q.H = static_cast<const unsigned char *>(p.H) + (size_t)w0 * p.U * p.B * c;
+            q.y = static_cast<const unsigned char *>(p.y) + (size_t)v0 * p.B * c;
+            if (p.g_in) q.g_in = p.g_in + w0 * p.U;
+            if (p.dinv_in) q.dinv_in = p.dinv_in + d0;
+            if (p.p_in) q.p_in = p.p_in + d0;
+            if (p.z) q.z = p.z + v0 * p.U;
+            if (p.llr) q.llr = p.llr + v0 * p.U * p.Q;
+            if (p.z_hist) q.z_hist = p.z_hist + v0 * p.K * p.U;
+            const hipError_t e = launch_gram_k<UP, SY, F16, BOX, VEC, HALF, NW>(q, s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    Params q = p;
     if (q.stagger > 0) {
         int per_cu = 0;
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(

@@ -452,7 +452,9 @@ static hipError_t launch_grad_k(const Params &p, int max_blocks, size_t limit, h
     const int tsyms = grad_tile_symbols<UP, SY, TRAIN, NW>(p, limit);
     if (!tsyms) return hipErrorInvalidValue;
     const int ntiles = (p.W + M::SG - 1) / M::SG * ((p.S + tsyms - 1) / tsyms);
-    const int grid = ntiles < max_blocks ? ntiles : max_blocks;
+    const int most = (int)groups_per_launch(1, GRAM_THREADS);
+    const int limited = max_blocks < most ? max_blocks : most;
+    const int grid = ntiles < limited ? ntiles : limited;
     auto fn = grid < ntiles ? k_gram_grad<UP, SY, F16, BOX, TRAIN, NW, true>
                             : k_gram_grad<UP, SY, F16, BOX, TRAIN, NW, false>;
     const size_t lds = M::bytes(tsyms, p.K, p.U);

@@ -63,9 +63,15 @@ static hipError_t launch_jobs_k(const JobDesc *jobs, const TileDesc *tiles, unsi
                                 int ntiles, int persistent, hipStream_t s)
 {
     if (!persistent) {
-        hipLaunchKernelGGL((k_jobs_gram<UP, F16, BOX, false>), dim3(ntiles), dim3(GRAM_THREADS), 0, s,
-                           jobs, tiles, next, ntiles);
-        return hipGetLastError();
+        const int most = (int)groups_per_launch(1, GRAM_THREADS);
+        for (int t0 = 0; t0 < ntiles; t0 += most) {
+            const int n = ntiles - t0 < most ? ntiles - t0 : most;
+            hipLaunchKernelGGL((k_jobs_gram<UP, F16, BOX, false>), dim3(n), dim3(GRAM_THREADS), 0, s,
+                               jobs, tiles + t0, next, n);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
     }
     auto fn = k_jobs_gram<UP, F16, BOX, true>;
     int per_cu = 0, grid = ntiles;

@@ -20,7 +20,8 @@ int main()
 {
     int B, U, W, S, K;
     while (std::scanf("%d %d %d %d %d", &B, &U, &W, &S, &K) == 5)
-        std::printf("%d %d\n", (int)ocd::gram_form(B, U, W, S, K), (int)ocd::gram_gradient(B, U, W, S, K));
+        if (U == 0) std::printf("%ld\n", ocd::groups_per_launch(B, W));   // blocks, -, threads
+        else std::printf("%d %d\n", (int)ocd::gram_form(B, U, W, S, K), (int)ocd::gram_gradient(B, U, W, S, K));
 }
 """
 
@@ -38,13 +39,13 @@ def forms(tmp_path_factory):
     def run(shapes):
         text = "\n".join(" ".join(map(str, s)) for s in shapes)
         out = subprocess.run([str(d / "forms")], input=text, capture_output=True, text=True, check=True)
-        return [tuple(bool(int(x)) for x in line.split()) for line in out.stdout.splitlines()]
+        return [tuple(int(x) for x in line.split()) for line in out.stdout.splitlines()]
     return run
 
 
 def test_the_benchmarks_rule_is_the_librarys(forms):
     for shape, (det, _) in zip(SHAPES, forms(SHAPES)):
-        assert bool(bench.gram_form(*shape)) == det, shape
+        assert bench.gram_form(*shape) == bool(det), shape
 
 
 def test_gradients_are_in_the_gram_form_on_fewer_shapes(forms):
@@ -65,3 +66,10 @@ def test_gradients_are_in_the_gram_form_on_fewer_shapes(forms):
 ])
 def test_shapes_beside_the_lines(forms, shape, det, grad):
     assert forms([shape]) == [(det, grad)]
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 3, 63, 1 << 20])
+@pytest.mark.parametrize("threads", [64, 128, 256])
+def test_a_launch_stays_below_2_to_the_32_threads(forms, blocks, threads):
+    (groups,), = forms([(blocks, 0, threads, 0, 0)])
+    assert groups * blocks * threads < 2**32 <= (groups + 1) * blocks * threads

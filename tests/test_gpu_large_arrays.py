@@ -99,3 +99,37 @@ def test_training_step_over_four_gib(ocd):
     assert torch.equal(dy, dy2)
     assert torch.isfinite(loss).all() and float(a.abs().max()) > 0
     _check_sampled(wl, z, L, np.array([0, W // 2, W - 1]), K, Q, "box", N0, beta=beta)
+
+
+def test_more_workgroups_than_a_launch_takes_gram_form(ocd):
+    """70 million subcarriers of 2 x 1: 17.5 million workgroups of 256 threads, more than
+    2^32 threads.  Both ends and the subcarriers around the second launch's first, bit for
+    bit as in calls of their own."""
+    B, U, W, S, Q, K = 2, 1, 70_000_000, 3, 2, 24
+    say("70 million subcarriers, Gram form")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    H = torch.randn(W, U, B, dtype=torch.complex64, device="cuda", generator=g)
+    y = torch.randn(W, S, B, dtype=torch.complex64, device="cuda", generator=g)
+    z, L, _ = ocd.detect(H, y, K, Q, "mmse", 0.1)
+    most = (2**32 - 1) // 256 * 4
+    for w in (0, most - 5, most, W - 9):
+        z1, L1, _ = ocd.detect(H[w:w + 9].contiguous(), y[w:w + 9].contiguous(), K, Q, "mmse", 0.1)
+        torch.cuda.synchronize()
+        assert torch.equal(z1, z[w:w + 9]) and torch.equal(L1, L[w:w + 9]), w
+    assert bool(torch.isfinite(torch.view_as_real(z)).all())
+
+
+def test_more_workgroups_than_a_launch_takes_fixed_point(ocd):
+    """70 million tiles of 64 threads, more than 2^32 threads, as above."""
+    B, U, W, S, Q, K = 2, 1, 70_000_000, 7, 2, 1
+    say("70 million subcarriers, fixed point")
+    g = torch.Generator(device="cuda").manual_seed(6)
+    H = torch.randint(-3000, 3000, (W, U, B, 2), dtype=torch.int16, device="cuda", generator=g)
+    y = torch.randint(-3000, 3000, (W, S, B, 2), dtype=torch.int16, device="cuda", generator=g)
+    z, _ = ocd.detect_fixed(H, y, K, Q, "mmse", 0.1, want_llr=False)
+    most = (2**32 - 1) // 64
+    for w in (0, most - 5, most, W - 9):
+        z1, _ = ocd.detect_fixed(H[w:w + 9].contiguous(), y[w:w + 9].contiguous(), K, Q, "mmse", 0.1,
+                                 want_llr=False)
+        torch.cuda.synchronize()
+        assert torch.equal(z1, z[w:w + 9]), w
