@@ -316,3 +316,77 @@ def test_error_on_ill_conditioned_channels(ocd, B, U, K, storage, kind):
         ocd.ocd_set_plan(pb, plan)
         say("  residual form %.3g" % r)
         assert e <= r
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("B,U,W,S,K", [(228, 12, 601, 14, 3), (230, 12, 514, 9, 3)])
+def test_one_wave_training_step_of_more_than_8_symbols(ocd, B, U, W, S, K, storage):
+    """9 to 16 users, more than 8 symbols and more than 512 subcarriers: the training step on
+    one wave a subcarrier, 16 symbols of z history for each of four, against the oracle."""
+    test_gram_gradients_edges(ocd, (B, U, W, S, 4, K, "hybrid", storage))
+
+
+LOOPS = [
+    # B, U, W, S, K, subcarriers of a part: more tiles than workgroups (the partial sums of
+    # 1 MiB), whose kernels take several tiles each
+    (64, 8, 4100, 3, 256, 1000),     # adjoint one wave a subcarrier, training step four
+    (64, 16, 4100, 1, 256, 1000),
+    (34, 17, 1100, 1, 256, 500),
+    (64, 8, 210000, 3, 4, 42000),    # training step on one wave a subcarrier
+]
+
+
+@pytest.mark.parametrize("case", LOOPS, ids=["-".join(map(str, c)) for c in LOOPS])
+def test_gradients_of_more_tiles_than_workgroups(ocd, case):
+    """The looping gradient kernels against parts of the subcarriers with a workgroup per
+    tile: z, LLRs and the adjoint's dy bit for bit, the training step's dy (whose mean has
+    another 1 / n) to 1e-6, dlambda, dbeta and the loss against the parts' sums (1e-4: FP32
+    partial sums in another order); and one part against the oracle."""
+    B, U, W, S, K, part = case
+    Q, mode, beta = 4, "hybrid", float(np.float32(0.8))
+    say("looping gradients", case)
+    wl = synth.make_workload_device(B, U, W, S, Q, 10.0, seed=2160 + U, device="cuda")
+    N0 = float(np.float32(wl["N0"]))
+    lam = (N0 * np.linspace(0.8, 1.3, K)).astype(np.float32)
+    H, y, bits, kw = wl["H"], wl["y"], wl["bits"], dict(lam=dev(lam))
+
+    def train(a, b):
+        loss, dlam, dbeta, dy, z, L = ocd.train_step(H[a:b], y[a:b], bits[a:b], K, Q, mode, N0, 1.0,
+                                                     beta, want_z=True, want_llr=True, **kw)
+        return z, L, dy, [t.double() for t in (loss, dlam, dbeta)]
+
+    def adjoint(a, b, dllr):
+        _, _, zh = ocd.detect(H[a:b], y[a:b], K, Q, mode, N0, 1.0, beta, want_hist=True, **kw)
+        dlam, dbeta, dy = ocd.backward(H[a:b], y[a:b], zh, dllr, K, Q, mode, N0, 1.0, beta, **kw)
+        return dy, [t.double() for t in (dlam, dbeta)]
+
+    z, L, dy, means = train(0, W)
+    dllr = torch.randn(W, S, U, Q, generator=torch.Generator(device="cuda").manual_seed(8), device="cuda")
+    loops = K > 100   # the adjoint's workgroups loop at this K only
+    dya, sums = adjoint(0, W, dllr) if loops else (None, [])
+    want = [torch.zeros_like(t) for t in means + sums]
+    for a in range(0, W, part):
+        b = min(a + part, W)
+        z1, L1, dy1, m = train(a, b)
+        assert torch.equal(z1, z[a:b]) and torch.equal(L1, L[a:b]), a
+        assert float((dy1 * ((b - a) / W) - dy[a:b]).norm()) <= 1e-6 * float(dy[a:b].norm()), a
+        m = [t * ((b - a) / W) for t in m]
+        if loops:
+            dy1, s = adjoint(a, b, dllr[a:b])
+            assert torch.equal(dy1, dya[a:b]), a
+            m += s
+        for t, x in zip(want, m):
+            t += x
+    for x, t in zip(means + sums, want):
+        assert float((x - t).norm()) <= 1e-4 * float(t.norm())
+    n = 40
+    Hh, yh, bh = host(H[:n]), host(y[:n]), host(bits[:n])
+    _, Lp, dyp, (loss, dlam, dbeta) = train(0, n)
+    Lh = host(Lp).astype(np.float64)
+    g = (1.0 / (1.0 + np.exp(-Lh)) - bh) / Lh.size
+    dlam_o, dbeta_o, dy_o = oracle.grad(Hh, yh, g, K, Q, mode, N0=N0, lam=lam, beta=beta)
+    for x, t in ((dlam, dlam_o), (dyp, dy_o), (dbeta, dbeta_o)):
+        x, t = host(x).ravel(), np.asarray(t).ravel()
+        assert np.linalg.norm(x - t) <= GRAD_TOL * np.linalg.norm(t)
+    mean = np.mean(np.logaddexp(0.0, np.where(bh != 0, -Lh, Lh)))
+    assert abs(float(loss) - mean) <= 1e-5 * mean
