@@ -28,7 +28,6 @@ struct Params {
     float lam_default;   // regulariser when lambda == nullptr
     float sqEs;          // sqrt(Es)
     float qscale;        // level spacing of the unit-energy square QAM
-    double llr_a, llr_c; // 1 / (sqEs qscale) and qscale^2 in FP64 (Gram form)
     float invU;          // 1 / U (slot of a staged H row without an integer divide)
     unsigned divS_m;     // n / S = divide_invariant(n, divS_m, divS_s1, divS_s2) (see
     int divS_s1, divS_s2;// set_divisor): exact, with no integer divide on the GPU
@@ -53,6 +52,9 @@ struct Params {
     float *dlambda;      // [K] adjoint output
     float *dbeta;        // [1] adjoint output
     float *loss;         // [1] training step: mean cross-entropy of the LLRs, or nullptr
+    // Gram form only; last, as every kernel's argument loads follow this order (explicit MMSE,
+    // 128 x 8, 1200 x 14: 14.89 us with these two before invU, 14.78 here)
+    double llr_a, llr_c; // 1 / (sqEs qscale) and qscale^2 in FP64
 };
 
 // Unsigned 32-bit division by a divisor d fixed for a launch, as a multiply-high,
