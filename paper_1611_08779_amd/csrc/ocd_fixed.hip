@@ -15,8 +15,8 @@
 // Two forms: tiles of 16 symbols on the integer matrix cores (k_fixed_tile) and, for few
 // symbols a subcarrier or many antennas, lane groups (k_forward_fx).
 //
-// Lane groups: L lanes per vector; lane j holds residual entries b = j + L i.  The updates run in FP64 on integer values: every intermediate of
-// the datapath is an integer below 2^53 (products below 2^32, sums below 2^41,
+// Lane groups: L lanes per vector; lane j holds residual entries b = j + L i.  The
+// updates run in FP64 on integer values: every intermediate of the datapath is an integer below 2^53 (products below 2^32, sums below 2^41,
 // d^-1 times a shifted inner product below 2^51), so every FP64 operation on them
 // is exact, a floor after a power-of-two scale is the arithmetic shift, and
 // clamps are the saturation; MI355X runs FP64 FMAs at the FP32 vector rate.  The

@@ -15,13 +15,15 @@ inline long groups_per_launch(long blocks, int threads)
 // (ocd_forward_reg.hip), where the residual form takes 0.24-0.9 of the Gram form's time up
 // to S = 2.  Elsewhere the contraction costs the same whatever K is, for 8, 16 or 32 users,
 // and once for every 16 symbols, and the residual form grows with U K, from 17 users on
-// (whose tiles of 32 x 32 hide less) with B U K.  Up to two tiles a compute unit the latency of a
-// workgroup counts, which the Gram form's fewer steps shorten: 0.3-0.9 of the time on either
-// side of the later lines.  Time of the Gram form over the residual form's where those keep the residual, FP32:
-//   base                 U = 4, K = 1, 2: 0.9-1.35; U = 9, K = 1, 2: 0.9-1.16; 40 x 17, K = 1 to 4:
-//                        0.9-1.54; 64 x 24, K = 1, 2: 0.9-1.19
+// (whose tiles of 32 x 32 hide less) with B U K.  Up to two tiles a compute unit the latency
+// of a workgroup counts, which the Gram form's fewer steps shorten: 0.3-0.9 of the time on
+// either side of the later lines.  Time of the Gram form over the residual form's where the
+// lines keep the residual, FP32 (the first with the quicker FP32 products):
+//   few updates          U = 4, K = 1, 2: 0.9-1.35; U = 9, K = 1, 2: 0.9-1.16; 40 x 17, K = 1 to
+//                        4: 0.9-1.54; 64 x 24, K = 1, 2: 0.9-1.19
 //   a tile a third full  128 x 4, K = 4, S = 3: 1.12, 256 x 4: 1.29; S = 7: 0.80, 0.86;
-//                        64 x 9, K = 4, S = 1, 3: 1.14, 1.10; S = 7: 0.91; 512 x 20, K = 1: 1.07-1.74
+//                        64 x 9, K = 4, S = 1, 3: 1.14, 1.10; S = 7: 0.91; 512 x 20, K = 1:
+//                        1.07-1.74
 //   S = 17               128 x 12, K = 2: 1.19, K = 4: 0.84; 256 x 32, K = 2: 1.18, K = 4: 0.69;
 //                        128 x 24, K = 2, 4: 1.65, 1.13; S = 14: 1.12, 0.77
 inline bool gram_form(int B, int U, int W, int S, int K)
@@ -49,12 +51,16 @@ inline bool gram_form(int B, int U, int W, int S, int K)
 //                    K = 1: 1.0, 1.34; K = 2: 0.97, 0.85
 //   U > 8, S = 17    128 x 16, K = 4: 1.54, 1.08; 256 x 16, K = 4: 1.10, 1.02; 128 x 32,
 //                    K = 2: 1.63, 1.47; K = 4: 1.01, 1.17
-//   S = 8            128 x 4, K = 4: 1.13, 1.25; 128 x 32, K = 1: 1.19, 1.25; 256 x 16, K = 2: 1.11, 1.25
-// Past 2048 subcarriers, one layer of the one-wave workgroups, few antennas or a tile that the
-// users do not fill leave the residual form the faster, at 2500 to 14000 subcarriers, S = 4,
-// K = 4: 32 x 8 1.00-1.42, 1.12-1.62; 64 x 4 1.00-1.61, 1.13-1.82; 64 x 9 0.84-1.39, 1.20-1.98; 32 x 16
-// 0.76-1.29, 1.09-1.61; against 64 x 8 0.68-0.75, 0.77-1.25; 128 x 8 0.63-0.71, below 1; 64 x 16 0.63,
-// 1.11 or less.
+//   S = 8            128 x 4, K = 4: 1.13, 1.25; 128 x 32, K = 1: 1.19, 1.25; 256 x 16, K = 2:
+//                    1.11, 1.25
+// Past 2048 subcarriers, one layer of the one-wave workgroups, few antennas or a tile that
+// the users do not fill leave the residual form the faster; training step and adjoint at 2500
+// to 14000 subcarriers, S = 4, K = 4:
+//   residual         32 x 8 1.00-1.42, 1.12-1.62; 64 x 4 1.00-1.61, 1.13-1.82; 64 x 9
+//                    0.84-1.39, 1.20-1.98; 32 x 16 0.76-1.29, 1.09-1.61
+//   Gram             64 x 8 0.68-0.75, 0.77-1.25; 128 x 8 0.63-0.71, below 1; 64 x 16 0.63,
+//                    up to 1.11; 64 x 24 0.57-0.73, 1.11-1.46
+// (where one gains more than the other loses, the gradients stay in the Gram form).
 inline bool gram_gradient(int B, int U, int W, int S, int K)
 {
     const int n = U * K;

@@ -34,10 +34,10 @@
 //      clip, a DPP broadcast of Delta from its owner and two FMAs; what else it takes is
 //      formed once per sweep.
 // What bounds it: the latency of that chain and of the loads before it, at the workgroups
-// whose registers fit a compute unit (three above 16 users), then the FP64 and matrix issue.  Against the residual form
-// (two passes over the antennas per update): 1200 x 14 vectors of 128 x 8, 3 sweeps,
-// 27.7 -> 11.8 us; 4200 x 14 in FP16 storage 64 -> 26.5 us; 3300 x 14 of 256 x 32, box, 5
-// sweeps 544 -> 193 us.
+// whose registers fit a compute unit, then the FP64 matrix products (113 cycles each) and the
+// FP64 issue.  Time of a call against the residual form (two passes over the antennas per
+// update): 1200 x 14 vectors of 128 x 8, 3 sweeps, 28.0 -> 14.2 us; 4800 x 14 in FP16 storage
+// 65.7 -> 27.9; 3300 x 14 of 256 x 32, box, 5 sweeps 546 -> 239.
 #pragma once
 
 #include <type_traits>
@@ -350,12 +350,12 @@ __device__ __forceinline__ void gram_contract(const Params &P, const unsigned ch
     }
     // two blocks in turn, each loaded again as soon as it is multiplied, with no copy or
     // branch, either of which would wait for the loads: past its end a wave reads its last
-    // block again.  (Four blocks in flight take registers that are worth more as waves:
-    // 3300 x 14 vectors of 256 x 32 in 235 us, not 218, 4200 x 14 of 128 x 16 in 61, not 52.)
-    // The barrier after the last pass waits for that pass's loads: four waves on few users,
-    // whose passes are few, peel it (1200 x 14 vectors of 128 x 8: 14.9 us without, 12.0
-    // with); elsewhere the second copy of the products costs more than it saves (24 uneven
-    // jobs: 860 us without, 1580 with)
+    // block again.  (Four blocks in flight take registers that are worth more as waves: 1.08
+    // times as long at 256 x 32, 1.17 at 128 x 16, measured with FP32 products.)  The barrier
+    // after the last pass waits for that pass's loads: four waves on few users, whose passes
+    // are few, peel it (1200 x 14 vectors of 128 x 8: 15.0 us without, 14.9 with, in FP16
+    // storage 13.3 and 11.8; 700 x 7 of 128 x 4 9.0 and 8.5); elsewhere it changes nothing and
+    // is a second copy of the products
     constexpr bool PEEL = NW == 4 && UP == 8;
     GramBlock<Sh::HR, F16> x0, x1;
     auto load = [&](GramBlock<Sh::HR, F16> &x, int blk) {
@@ -830,9 +830,9 @@ __device__ __forceinline__ void gram_sweeps(const Params &P, long w0, int s0, in
 
 // Whether the contraction of FP16 storage takes FP16 operands (exact products, FP32 sums of
 // eight): where z then errs no more than in the residual form on any of the channels above
-// (16 antennas a user, up to 8 users and 16 sweeps: 0.6 to 0.99 times at users correlated
-// 0.99; 256 x 16, 1.11 at 16 sweeps; 64 x 16, 1.2).  4800 x 14 vectors of 128 x 8 30 us against 40 in
-// FP64, 1200 x 14 11.8 against 14.8.
+// (16 antennas a user, up to 8 users and 16 sweeps: 0.7 to 0.99 times at the worst; 128 x 8
+// at 32 sweeps 1.03, 256 x 16 at 16 1.11, 128 x 16 1.09).  4800 x 14 vectors of 128 x 8 30 us
+// against 40 in FP64, 1200 x 14 11.8 against 14.8.
 __host__ __device__ inline bool gram_half(int B, int U, int K)
 {
     return U <= 8 && B >= 16 * U && K <= 16;

@@ -21,8 +21,8 @@
 namespace ocd {
 
 // Whether one wave takes a subcarrier (see gram_waves): from two tiles a compute unit on, or
-// where four waves share long sweeps or contractions, from three or four.  Time with one wave over time with
-// four, K = 4, at 520 / 700 / 1000 subcarriers:
+// where four waves share long sweeps or contractions, from three or four.  Time with one
+// wave over time with four, K = 4, at 520 / 700 / 1000 subcarriers:
 //   adjoint         128 x 4, S = 8: 0.96 / 0.90 / 0.79;   64 x 8, S = 14: 1.09 / 1.00 / 0.88;
 //                   128 x 16, S = 4: 0.63 / 0.60 / 0.59;  256 x 16, S = 14: 1.06 / 1.01 / 0.94
 //   training step   32 x 8, S = 8: 0.90 / 0.84 / 0.75;    64 x 8, S = 14: 1.15 / 1.08 / 0.96;

@@ -1,9 +1,9 @@
 // ocd_jobs.hip -- uneven detection jobs in one persistent launch.
 //
 // Every job is cut into tiles of consecutive (subcarrier, symbol) vectors.  A
-// tile runs exactly the one-problem code: gram_tile for a job in the Gram form (one
-// subcarrier a tile, ocd_jobs_gram.hip, a kernel per user bound), else forward_tile.  The lanes per vector
-// follow from the complex entries each lane holds (NPL): a job with B antennas
+// tile runs exactly the one-problem code: gram_tile for a job in the Gram form (whole
+// subcarriers and 16 symbols, ocd_jobs_gram.hip, a kernel per user bound), else
+// forward_tile.  The lanes per vector follow from the complex entries each lane holds (NPL): a job with B antennas
 // uses L = B / NPL lanes (4, 8, 16 or 32).  The batch tuner picks one of three
 // lane modes for the whole batch: NPL = 8 for every job; NPL = 16 for jobs with
 // B >= 256 (half the lanes per vector: no reduction across DPP rows) and 8 for
@@ -351,7 +351,7 @@ static hipError_t enqueue_jobs(const JobsPlan &jp, unsigned char *ws, int persis
                                                                jp.jobs.size() * sizeof(JobDesc));
     const int *first = jp.tiles->first;
     if (persistent) hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, s, next);
-    // the kernels with the longest tiles first
+    // the Gram form's kernels, the most users (and the longest tiles) first, then the residual's
     for (int k = N_JOB_KERNELS - 1; k >= 1; --k) {
         if (first[k] == first[k + 1]) continue;
         const hipError_t e = launch_jobs_gram(k, jp.f16, jp.box, jobs, tiles + first[k], next + k,
