@@ -66,10 +66,12 @@ def gram_form(B, U, W, S, K):
         return False
     if U <= 8:
         return not (U <= 4 and S <= 4 and n < 24 and tiles > (2048 if B >= 128 else 12000))
+    if U <= 10 and B * U < 1024 and n < 50 and tiles > 3072:
+        return False
     if S > 16:
         return tiles <= 512 or B > 256 or (K >= 3 if U <= 16 else B * n >= 24576)
     if U <= 16:
-        return not (U <= 10 and S <= 4 and n < 40 and tiles > 4096)
+        return True
     return not (S >= 3 and n < 32) and not (U <= 24 and K <= 2 and S > 8 and tiles > 512)
 
 

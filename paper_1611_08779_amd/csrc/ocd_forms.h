@@ -22,8 +22,8 @@ inline long groups_per_launch(long blocks, int threads)
 //   few updates          U = 4, K = 1, 2: 0.9-1.35; U = 9, K = 1, 2: 0.9-1.16; 40 x 17, K = 1 to
 //                        4: 0.9-1.54; 64 x 24, K = 1, 2: 0.9-1.19
 //   a tile a third full  128 x 4, K = 4, S = 3: 1.12, 256 x 4: 1.29; S = 7: 0.80, 0.86;
-//                        64 x 9, K = 4, S = 1, 3: 1.14, 1.10; S = 7: 0.91; 512 x 20, K = 1:
-//                        1.07-1.74
+//                        512 x 20, K = 1: 1.07-1.74; from 3072 tiles on 64 x 9, K = 4: 1.03-
+//                        1.14, 18 x 9 1.03-1.37, 26 x 9, K = 3: 1.25 (0.87-0.98 at 2400)
 //   S = 17               128 x 12, K = 2: 1.19, K = 4: 0.84; 256 x 32, K = 2: 1.18, K = 4: 0.69;
 //                        128 x 24, K = 2, 4: 1.65, 1.13; S = 14: 1.12, 0.77
 inline bool gram_form(int B, int U, int W, int S, int K)
@@ -33,9 +33,10 @@ inline bool gram_form(int B, int U, int W, int S, int K)
     if (!base || B < 2 * U || (U <= 8 && S < 3 && B <= 256)) return false;
     const long tiles = (long)W * ((S + 15) / 16);
     if (U <= 8) return !(U <= 4 && S <= 4 && n < 24 && tiles > (B >= 128 ? 2048 : 12000));
+    if (U <= 10 && B * U < 1024 && n < 50 && tiles > 3072) return false;
     if (S > 16)
         return tiles <= 512 || B > 256 || (U <= 16 ? K >= 3 : (long)B * n >= 24576);
-    if (U <= 16) return !(U <= 10 && S <= 4 && n < 40 && tiles > 4096);
+    if (U <= 16) return true;
     return !(S >= 3 && n < 32) && !(U <= 24 && K <= 2 && S > 8 && tiles > 512);
 }
 

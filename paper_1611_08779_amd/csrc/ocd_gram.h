@@ -34,8 +34,8 @@
 //      clip, a DPP broadcast of Delta from its owner and two FMAs; what else it takes is
 //      formed once per sweep.
 // What bounds it: the latency of that chain and of the loads before it, at the workgroups
-// whose registers fit a compute unit, then the FP64 matrix products (113 cycles each) and the
-// FP64 issue.  Time of a call against the residual form (two passes over the antennas per
+// whose registers fit a compute unit, then the FP64 matrix products (64 cycles each: 0.50 of
+// the time at 256 x 32, 0.36 at 128 x 8) and the vector issue (0.43, 0.30).  Time of a call against the residual form (two passes over the antennas per
 // update): 1200 x 14 vectors of 128 x 8, 3 sweeps, 28.0 -> 14.2 us; 4800 x 14 in FP16 storage
 // 65.7 -> 27.9; 3300 x 14 of 256 x 32, box, 5 sweeps 546 -> 239.
 #pragma once
