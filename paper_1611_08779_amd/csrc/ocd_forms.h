@@ -61,7 +61,10 @@ inline bool gram_form(int B, int U, int W, int S, int K)
 //                    0.84-1.39, 1.20-1.98; 32 x 16 0.76-1.29, 1.09-1.61
 //   Gram             64 x 8 0.68-0.75, 0.77-1.25; 128 x 8 0.63-0.71, below 1; 64 x 16 0.63,
 //                    up to 1.11; 64 x 24 0.57-0.73, 1.11-1.46
-// (where one gains more than the other loses, the gradients stay in the Gram form).
+// (where one gains more than the other loses, the gradients stay in the Gram form).  Where
+// workgroups take several tiles each, their loop costs registers, K = 4: 128 x 8 0.84, 1.46;
+// 64 x 8 1.15, 2.05; 64 x 24 0.95, 1.78; against 64 x 16 0.57, 1.00; 128 x 24 0.95, 0.84; and
+// 64 x 8, K = 20, 0.71, 1.17.
 inline bool gram_gradient(int B, int U, int W, int S, int K)
 {
     const int n = U * K;
@@ -69,6 +72,9 @@ inline bool gram_gradient(int B, int U, int W, int S, int K)
     if (!gram_form(B, U, 1, S, K)) return false;
     if (U <= 8 && S > 16) return tiles <= 256 || (n >= 24 && work >= 2048);
     if (tiles <= 512) return true;
+    // more workgroups (of four subcarriers, or one) than the static scratch has partial sums for
+    const long groups = U <= 16 ? tiles / 4 : tiles;
+    if (groups > 262080 / (K + 1) && K <= 8 && (U <= 8 || (U > 16 && B * U < 2048))) return false;
     if (tiles > 2304 && U <= 16) {
         const int full = U <= 4 ? 1024 : U <= 8 ? 512 : U <= 12 ? 1024 : 520;
         if (B * U < full) return false;

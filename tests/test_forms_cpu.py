@@ -62,7 +62,8 @@ def test_gradients_are_in_the_gram_form_on_fewer_shapes(forms):
     ((32, 8, 1000, 17, 2), True, False), ((128, 24, 988, 17, 2), False, False),
     ((128, 24, 123, 17, 2), True, True), ((256, 32, 988, 17, 4), True, True),
     ((64, 9, 5600, 3, 4), False, False), ((64, 9, 2300, 3, 4), True, True),
-    ((32, 8, 6000, 4, 4), True, False), ((128, 8, 6000, 4, 4), True, True), ((512, 20, 150, 14, 1), False, False),
+    ((32, 8, 6000, 4, 4), True, False), ((128, 8, 6000, 4, 4), True, True),
+    ((64, 8, 230000, 3, 4), True, False), ((64, 16, 230000, 2, 4), True, True), ((512, 20, 150, 14, 1), False, False),
 ])
 def test_shapes_beside_the_lines(forms, shape, det, grad):
     assert forms([shape]) == [(det, grad)]

@@ -332,7 +332,7 @@ LOOPS = [
     (64, 8, 4100, 3, 256, 1000),     # adjoint one wave a subcarrier, training step four
     (64, 16, 4100, 1, 256, 1000),
     (34, 17, 1100, 1, 256, 500),
-    (64, 8, 210000, 3, 4, 42000),    # training step on one wave a subcarrier
+    (64, 8, 106000, 3, 9, 30000),    # training step on one wave a subcarrier
 ]
 
 
