@@ -844,11 +844,11 @@ __host__ __device__ __forceinline__ auto gram_dispatch(const Params &P, F &&f)
 {
     using std::false_type;
     using std::true_type;
-    if (!P.vec_ok) return f(false_type{}, false_type{});
     if constexpr (F16 && UP == 8) {
-        if (gram_half(P.B, P.U, P.K)) return f(true_type{}, true_type{});
+        if (gram_half(P.B, P.U, P.K))
+            return P.vec_ok ? f(true_type{}, true_type{}) : f(false_type{}, true_type{});
     }
-    return f(true_type{}, false_type{});
+    return P.vec_ok ? f(true_type{}, false_type{}) : f(false_type{}, false_type{});
 }
 
 // This wave's subcarrier of a workgroup whose first is w0.
