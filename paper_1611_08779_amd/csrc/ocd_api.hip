@@ -139,6 +139,12 @@ static int reg_user_bound(int U, int npl)
     return (U <= 8 && npl <= 8) ? 8 : 0;
 }
 
+// LDS that a gradient plan leaves to its kernels; the Gram form takes no LDS of a plan.
+static size_t gradient_static_lds(const ocd_problem *pb)
+{
+    return gram_gradient(pb->B, pb->U, pb->W, pb->S, pb->K) ? 0 : GRADIENT_STATIC_LDS;
+}
+
 bool make_params(const ocd_problem *pb, const ocd_plan &pl, const float *lambda, bool backward,
                  Params &P, int &npl, int &threads, size_t &lds, int min_npl)
 {
@@ -187,7 +193,7 @@ bool make_params(const ocd_problem *pb, const ocd_plan &pl, const float *lambda,
         return true;
     }
     lds = lds_bytes(P, threads / L, backward, threads / 64);
-    return lds + (backward ? GRADIENT_STATIC_LDS : 0) <= (size_t)lds_limit_bytes();
+    return lds + (backward ? gradient_static_lds(pb) : 0) <= (size_t)lds_limit_bytes();
 }
 
 // Rough occupancy model used by the heuristic: lanes doing useful work per CU.
@@ -790,7 +796,7 @@ static bool train_params(const ocd_problem *pb, const ocd_plan &pl, const float 
 {
     if (!make_params(pb, pl, lambda, true, P, npl, threads, lds)) return false;
     lds = lds_bytes(P, threads / pl.lanes_per_vector, true, threads / 64, true);
-    return lds + GRADIENT_STATIC_LDS <= (size_t)lds_limit_bytes();
+    return lds + gradient_static_lds(pb) <= (size_t)lds_limit_bytes();
 }
 
 // The training step's plan: the one ocd_autotune_train cached for the shape, else

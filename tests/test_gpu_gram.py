@@ -390,3 +390,23 @@ def test_gradients_of_more_tiles_than_workgroups(ocd, case):
         assert np.linalg.norm(x - t) <= GRAD_TOL * np.linalg.norm(t)
     mean = np.mean(np.logaddexp(0.0, np.where(bh != 0, -Lh, Lh)))
     assert abs(float(loss) - mean) <= 1e-5 * mean
+
+
+def test_gradients_whose_residual_plan_ends_at_the_lds_limit(ocd):
+    """1024 x 19, K = 46: the residual form's smallest plan takes all but 104 bytes of the LDS
+    of a workgroup, less than its kernels' own; the Gram form, which runs here, does not
+    use it, so the call is accepted."""
+    B, U, W, S, Q, K = 1024, 19, 2, 2, 4, 46
+    say("residual plan at the limit")
+    wl = synth.make_workload(B, U, W, S, Q, 10.0, seed=[223, 0])
+    N0, beta = float(np.float32(wl["N0"])), float(np.float32(0.8))
+    lam = (N0 * np.linspace(0.8, 1.3, K)).astype(np.float32)
+    H, y, lt = dev(wl["H"]), dev(wl["y"]), dev(lam)
+    _, L, zh = ocd.detect(H, y, K, Q, "hybrid", N0, 1.0, beta, lam=lt, want_hist=True)
+    dllr = torch.randn(W, S, U, Q, generator=torch.Generator().manual_seed(4)).cuda()
+    dlam, _, dy = ocd.backward(H, y, zh, dllr, K, Q, "hybrid", N0, 1.0, beta, lam=lt)
+    torch.cuda.synchronize()
+    dlam_o, _, dy_o = oracle.grad(wl["H"], wl["y"], host(dllr), K, Q, "hybrid", N0=N0, lam=lam, beta=beta)
+    for a, b in ((dlam, dlam_o), (dy, dy_o)):
+        a, b = host(a).ravel(), np.asarray(b).ravel()
+        assert np.linalg.norm(a - b) <= GRAD_TOL * np.linalg.norm(b)
